@@ -986,6 +986,40 @@ __device__ __forceinline__ const uint32_t* uniform_ptr(const uint32_t* p) {
     return reinterpret_cast<const uint32_t*>((uint64_t)hi << 32 | lo);
 }
 
+// Sums of N values per lane over the 64 lanes of a wave: row r of 16 lanes
+// ends with the sum of v[4 k + (r >> 1 | (r & 1) << 1)] in out[k].  Every sum is the
+// tree that pairs lanes 32, 16, 8, 4, 2 and 1 apart, in that order.  The first
+// two levels put two values each into one register (a half of the wave, then
+// a row of it, keeps the sums of one); within a row, values repeat every 2 D
+// lanes by the time lanes D apart are added, so a rotation finds them.  The 28
+// float fields of a gradient record take 70 VALU instructions; a shuffle per
+// field and level took 168 adds and as many LDS permutes.
+template <typename T>
+__device__ __forceinline__ T swap_add32(T a, T b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b),
+                                                    false, false);
+    return __builtin_bit_cast(T, (uint32_t)r[0]) + __builtin_bit_cast(T, (uint32_t)r[1]);
+}
+template <typename T>
+__device__ __forceinline__ T swap_add16(T a, T b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b),
+                                                    false, false);
+    return __builtin_bit_cast(T, (uint32_t)r[0]) + __builtin_bit_cast(T, (uint32_t)r[1]);
+}
+template <int D, typename T>
+__device__ __forceinline__ T ror_add(T x) {
+    return x + __builtin_bit_cast(T, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x120 + D, 0xF, 0xF, false));
+}
+template <typename T, int N, int K>
+__device__ __forceinline__ void wave_sums(const T (&v)[N], T (&out)[K]) {
+    static_assert(K == (N + 3) / 4, "four values per register");
+    auto at = [&](int i) { return i < N ? v[i < N ? i : 0] : T(0); };
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        out[k] = ror_add<1>(ror_add<2>(ror_add<4>(ror_add<8>(
+            swap_add16(swap_add32(at(4 * k), at(4 * k + 1)), swap_add32(at(4 * k + 2), at(4 * k + 3)))))));
+}
+
 // One (scan, pose, tile) item: rasterization rounds, resolve, tile record.
 template <int TW, int TH, int MODE, bool OVF>
 __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs& a, const ItemInfo& it,
@@ -1258,49 +1292,38 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
 
     // ---------------------------------------------------------------- reduction (fixed order)
     constexpr int NF = MODE == kIcp ? 40 : (MODE == kGrad ? 39 : 12);
-    float v[NF];
-    v[0] = __int_as_float(acc.e_table);
+    // integer fields 0..10 and the color counts, then the float fields from 11 on
+    constexpr int NI = MODE == kIcp ? 11 : 13, NFl = MODE == kIcp ? 29 : (MODE == kGrad ? 28 : 1);
+    int vi[NI];
+    float vf[NFl];
+    vi[0] = acc.e_table;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) v[1 + k] = __int_as_float(acc.cnt[k]);
-    v[10] = __int_as_float(acc.n_active);
-    v[11] = acc.e_soft;
-    if (MODE == kGrad || MODE == kIcp) {
+    for (int k = 0; k < 9; ++k) vi[1 + k] = acc.cnt[k];
+    vi[10] = acc.n_active;
+    if constexpr (MODE != kIcp) { vi[11] = acc.col[0]; vi[12] = acc.col[1]; }
+    vf[0] = acc.e_soft;
+    if constexpr (MODE == kGrad || MODE == kIcp) {
 #pragma unroll
-        for (int k = 0; k < 6; ++k) v[12 + k] = acc.jtr[k];
+        for (int k = 0; k < 6; ++k) vf[1 + k] = acc.jtr[k];
 #pragma unroll
-        for (int k = 0; k < 21; ++k) v[18 + k] = acc.jtj[k];
+        for (int k = 0; k < 21; ++k) vf[7 + k] = acc.jtj[k];
     }
-    if (MODE == kIcp) v[39] = acc.sse;
-    int col0 = 0, col1 = 0;
-    if (MODE != kIcp && color) {
-        col0 = acc.col[0]; col1 = acc.col[1];
+    if constexpr (MODE == kIcp) vf[28] = acc.sse;
+    constexpr int KI = (NI + 3) / 4, KF = (NFl + 3) / 4;
+    int si[KI];
+    float sf[KF];
+    wave_sums(vi, si);
+    wave_sums(vf, sf);
+    if ((lane & 15) == 0) {
+        const int f0 = (lane >> 5) | ((lane >> 3) & 2);     // the fields this row of 16 lanes holds: 4 k + f0
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            col0 += __shfl_xor(col0, off);
-            col1 += __shfl_xor(col1, off);
+        for (int k = 0; k < KI; ++k) {
+            const int f = 4 * k + f0;
+            if (f < NI) red[wave][f <= 10 ? f : f + 28] = __int_as_float(si[k]);
         }
-    }
 #pragma unroll
-    for (int f = 0; f < NF; ++f) {
-        if (f <= 10) {
-            int x = __float_as_int(v[f]);
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-            v[f] = __int_as_float(x);
-        } else {
-            float x = v[f];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-            v[f] = x;
-        }
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) red[wave][f] = v[f];
-        if (MODE != kIcp) {
-            red[wave][39] = __int_as_float(col0);
-            red[wave][40] = __int_as_float(col1);
-        }
+        for (int k = 0; k < KF; ++k)
+            if (4 * k + f0 < NFl) red[wave][11 + 4 * k + f0] = sf[k];
     }
     __syncthreads();
     if (tid < kRecFields) {
