@@ -35,6 +35,13 @@ __device__ __forceinline__ void load_pose(const double* __restrict__ T, PoseF& P
     }
 }
 
+// A value that is the same in every lane, moved to scalar registers.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ float uniform(float x) { return __int_as_float(uniform(__float_as_int(x))); }
+__device__ __forceinline__ double uniform(double x) {
+    return __hiloint2double(uniform(__double2hiint(x)), uniform(__double2loint(x)));
+}
+
 __device__ __forceinline__ float3 cam_contract(const PoseF& P, float x, float y, float z) {
     const float d0 = (float)((double)x - P.t[0]);
     const float d1 = (float)((double)y - P.t[1]);
@@ -125,9 +132,11 @@ struct Tile {
 // snapshot (far more than the rounding between the FP64 plane and the f32 key).
 constexpr double kOccMargin = 1.0 + 1e-6;
 // The depth snapshot keeps one value per kSeg-pixel segment of each tile row
-// (index row * kSegs + x / kSeg) and the tile's farthest at kSnapTile.
+// (index row * kSegs + x / kSeg) and, from kSnapTile on, the farthest of each
+// wave's quarter of the tile.
+constexpr int kWaves = kWG / 64;
 constexpr int kSeg = 16, kSegs = 4, kSnapTile = 32 * kSegs;
-constexpr int kSnapEvery = 4;            // rounds between snapshot refreshes after the first ones
+constexpr int kSnapEvery = 4;            // chunks between snapshot refreshes after the first ones
 
 // Minimum of x over aligned groups of G consecutive lanes (G = 8 or 16, one
 // DPP row or half row): swaps inside quads, then the half-row and row
@@ -143,6 +152,39 @@ __device__ __forceinline__ uint32_t group_min(uint32_t x) {
     return x;
 }
 
+// Inclusive prefix sum and prefix maximum over the 64 lanes of a wave (DPP
+// row shifts, then the rows' last lanes broadcast to the rows above); a lane
+// without a source takes 0.  All lanes of the wave must be active.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp0(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ int wave_scan_add(int x) {
+    x += dpp0<0x111, 0xF>(x);          // row_shr 1, 2, 4, 8
+    x += dpp0<0x112, 0xF>(x);
+    x += dpp0<0x114, 0xF>(x);
+    x += dpp0<0x118, 0xF>(x);
+    x += dpp0<0x142, 0xA>(x);          // row_bcast 15 into rows 1 and 3
+    x += dpp0<0x143, 0xC>(x);          // row_bcast 31 into rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ int wave_scan_max(int x) {      // x >= 0
+    x = max(x, dpp0<0x111, 0xF>(x));
+    x = max(x, dpp0<0x112, 0xF>(x));
+    x = max(x, dpp0<0x114, 0xF>(x));
+    x = max(x, dpp0<0x118, 0xF>(x));
+    x = max(x, dpp0<0x142, 0xA>(x));
+    x = max(x, dpp0<0x143, 0xC>(x));
+    return x;
+}
+
+// Orders a wave's LDS accesses around it (LDS operations of one wave complete
+// in order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Farthest snapshot w over the segments that columns [x0, x1] of row y touch.
 __device__ __forceinline__ float snap_min(const float* rmin, int y, int x0, int x1) {
     const float* r = rmin + y * kSegs;
@@ -151,200 +193,292 @@ __device__ __forceinline__ float snap_min(const float* rmin, int y, int x0, int 
     return m;
 }
 
-// Small (sub-)triangles are rasterized by their own thread over the pixel
-// centres of their bounding box inside the tile (int32 edge functions).
-__device__ __forceinline__ void raster_small(uint64_t* keys, int tile_w, const Tile& tl, const float* rmin,
-                                             const int X[3], const int Y[3], int px0, int px1, int py0, int py1,
-                                             const WPlane& pl, double cx, double cy, uint32_t id) {
+// Every wave of a tile's workgroup rasterizes chunks of 64 triangles by
+// itself: each lane sets up one (sub-)triangle in its slot of the wave's LDS
+// queue, and the wave deals the rows of all of them out to its lanes, 64 at a
+// time.  Waves meet at no barrier before the resolve: the z-buffer only takes
+// maxima, and a depth snapshot of any age is a valid bound.  The pass is bound
+// by VALU issue (84 % of the rate on 64 poses of 640x480 against 1 M
+// triangles, 73 % of the lanes active), so what counts is instructions per
+// row and per triangle.  Before, a workgroup of 256 took rounds of 256
+// triangles with three barriers each, triangles of up to 64 px walked by their
+// own lane (three lanes of a wave busy on average) and larger ones queued as
+// two-row jobs with int64 edge tests: 60 % of the lanes active, 2.48 ms a
+// launch against 1.90 ms now.  Jobs of one row beat jobs of two (1.0 %) and
+// four (4 %).
+//
+// A row's covered span is exact without an edge test per pixel.  With the
+// vertices sorted by y (A, B, C), row r (y = 256 r, YA <= y < YC) lies
+// between the crossings of the long edge AC and of AB (y < YB) or BC.  A
+// crossing c = X + t dX/dY in 1/256 px is a fraction with denominator dY, so
+// its distance from a pixel centre is either zero or at least 1/|dY|.  With
+// all vertices within kSpanLimit = 2^23 of the tile origin, |dY| < 2^24 and
+// the FP64 error of c (slope to 1 ulp, no extrapolation beyond the edge) is
+// below 2^-27, so ceil((c - 2^-25) / 256) is exactly the first pixel at or
+// right of the crossing: the first covered one of a left edge (inclusive by
+// the top-left rule) and the first uncovered one of a right edge.  The rule
+// leaves out y = YC (bottom edges and vertices) and keeps y = YA.  Triangles
+// with farther vertices keep integer vertices in their slot and take the
+// int64 edge functions per pixel.
+constexpr int kSpanLimit = 1 << 23;
+constexpr double kSpanTie = 0x1p-33;       // 2^-25 / 256
+// Depth along a row is accumulated, w += a per pixel.  Small triangles start
+// at their box's corner and add b per row and a per pixel up to the span; the
+// others start at the span, from the even row of their pair of rows: so the
+// rounding of a fragment's depth depends on its triangle and pixel alone.
+constexpr int kSmallArea = 64;             // box pixels of a small triangle
+constexpr int kTinyArea = 9;               // box pixels walked by the triangle's own lane
+constexpr uint32_t kWideBox = 1u << 31, kSmallBox = 1u << 30, kStepBox = 1u << 29;
+
+struct WaveQueue {
+    double xa[64], xb[64];                 // (X - 2^-25) / 256 of A and B
+    double mac[64], mab[64], mbc[64];      // slopes, px per 1/256 px of y
+    int ya[64], yb[64];                    // tile-relative, 1/256 px
+    // (a wide slot holds its vertices (X, Y), tile-relative and of positive
+    // area, as int pairs in xa, xb and mac)
+    double pa[64], pb[64], w0[64];         // 1/z steps per pixel and row, and 1/z at the box's column px0: at
+                                           // row py0 of a small triangle, at v = cy of the others
+    uint32_t id[64];
+    uint32_t box[64];                      // tile-relative px0 | px1 << 6 | py0 << 12 | py1 << 18, and the k...Box flags
+    int base[64];                          // first job of the lane's triangle
+    int slot[64];
+};
+
+struct Queues {
+    WaveQueue w[kWaves];
+    // per kSeg-pixel segment of each tile row, the farthest w = 1/z held by
+    // its keys (0 if a pixel is empty) when it was last refreshed
+    float rowmin[kSnapTile + kWaves];
+};
+
+// n / d for integers of less than 2^25 (d != 0): reciprocal with two Newton
+// steps and a residual correction, within 1 ulp
+__device__ __forceinline__ double div_int(int n, int d) {
+    const double dn = (double)n, dd = (double)d;
+    double r = __builtin_amdgcn_rcp(dd);
+    r = fma(fma(-dd, r, 1.0), r, r);
+    r = fma(fma(-dd, r, 1.0), r, r);
+    const double q = dn * r;
+    return fma(fma(-dd, q, dn), r, q);
+}
+
+// A small triangle's 1/z at (x, y) of its box is w0 after y sums w += pb and x
+// sums w += pa, each rounded.  While all of them lie in one binade they are
+// multiples of one ulp, and a sum adds pa or pb rounded to that ulp, so that
+// w0 + y pb' + x pa' with the rounded steps is exact and the same value.  True,
+// with pa and pb replaced by their rounded values, where the box's corners
+// share a binade and neither step lies midway between two multiples (rounding
+// would then depend on the last bit of w); false: the sums must be taken one
+// by one.
+__device__ __forceinline__ bool exact_steps(double w0, double& pa, double& pb, int nx, int ny) {
+    const double odd = __hiloint2double(__double2hiint(w0), __double2loint(w0) ^ 1);
+    const double a = (w0 + pa) - w0, b = (w0 + pb) - w0;
+    const bool mid = (odd + pa) - odd != a || (odd + pb) - odd != b;     // (also where w0 is not finite)
+    const double wx = fma((double)nx, a, w0), wy = fma((double)ny, b, w0), wxy = fma((double)nx, a, wy);
+    const int e = __double2hiint(w0);
+    const uint32_t d = (uint32_t)((__double2hiint(wx) ^ e) | (__double2hiint(wy) ^ e) | (__double2hiint(wxy) ^ e));
+    if (mid || (d & 0xfff00000u)) return false;
+    pa = a;
+    pb = b;
+    return true;
+}
+
+// A triangle of a few pixels, walked by its own lane over its box (int32 edge
+// functions: spans below 2^14).
+__device__ __forceinline__ void raster_tiny(uint64_t* keys, int stride, const float* rmin, const Tile& tl, const int X[3], const int Y[3],
+                                            int px0, int px1, int py0, int py1, const WPlane& pl, double cx, double cy,
+                                            uint32_t id) {
+    const int area = (X[1] - X[0]) * (Y[2] - Y[0]) - (Y[1] - Y[0]) * (X[2] - X[0]);
+    if (area == 0) return;
     int E[3], sx[3], sy[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         const int k1 = k == 2 ? 0 : k + 1;
-        const int dx = X[k1] - X[k], dy = Y[k1] - Y[k];
+        int dx = X[k1] - X[k], dy = Y[k1] - Y[k];
+        if (area < 0) { dx = -dx; dy = -dy; }      // edges of the other orientation
         const bool topleft = dy < 0 || (dy == 0 && dx > 0);
         E[k] = dx * (256 * py0 - Y[k]) - dy * (256 * px0 - X[k]) - (topleft ? 0 : 1);
         sx[k] = -256 * dy;
         sy[k] = 256 * dx;
     }
     double wrow = fma(pl.b, (double)py0 - cy, fma(pl.a, (double)px0 - cx, pl.e));
+    uint64_t* row = keys + (py0 - tl.y0) * stride - tl.x0;
+#pragma unroll 1
     for (int y = py0; y <= py1; ++y) {
         int e0 = E[0], e1 = E[1], e2 = E[2];
         double w = wrow;
-        uint64_t* row = keys + (y - tl.y0) * tile_w - tl.x0;
-        // the plane's nearest point over the row's columns is behind everything
-        // visible in this row: every atomic below would leave the keys unchanged
-        const double wn = fmax(wrow, fma(pl.a, (double)(px1 - px0), wrow));
-        const int xend = wn * kOccMargin < (double)snap_min(rmin, y - tl.y0, px0 - tl.x0, px1 - tl.x0) ? px0 - 1 : px1;
-        // (the loop runs on the key address; the far plane is applied at
-        // the resolve, see there)
-        for (uint64_t *k = row + px0, *kend = row + xend; k <= kend; ++k) {
-            {   // branch-free: an uncovered pixel offers the empty key, which changes nothing
-                const float wf = (float)w;
-                const bool cov = (e0 | e1 | e2) >= 0;
-                atomicMax((unsigned long long*)k, cov ? (unsigned long long)pack_key(wf, id) : kEmptyKey);
-            }
+        // (a row of so few pixels is drawn without a look at the snapshot,
+        // except where a plane seen edge on leaves 1/z negative in the box)
+        const double we = fma(pl.a, (double)(px1 - px0), wrow);
+        const bool skip = fmin(wrow, we) < 0.0 && fmax(wrow, we) * kOccMargin <
+                                                      (double)snap_min(rmin, y - tl.y0, px0 - tl.x0, px1 - tl.x0);
+#pragma unroll 1
+        for (int x = skip ? px1 + 1 : px0; x <= px1; ++x) {
+            if ((e0 | e1 | e2) >= 0) atomicMax((unsigned long long*)(row + x), pack_key((float)w, id));
             e0 += sx[0]; e1 += sx[1]; e2 += sx[2];
             w += pl.a;
         }
         E[0] += sy[0]; E[1] += sy[1]; E[2] += sy[2];
         wrow += pl.b;
+        row += stride;
     }
 }
 
-// Larger (sub-)triangles are queued in LDS and rasterized by the whole
-// workgroup in jobs of kBand rows: a job brackets the covered span of each of
-// its rows between the three edge crossings (FP64, exact to far below a
-// pixel) and gives only pixel centres inside it the exact int64 edge test.
-constexpr int kQCap = 192;                 // queued sub-triangles per pass (more wait for the next); with the
-                                           // 16 KB z-buffer, 40 KB of LDS: four workgroups per CU
-constexpr int kBand = 2;                   // rows per job
-constexpr int kSmallArea = 64;             // bounding-box pixels rasterized by the owning thread
+// Setup of one (sub-)triangle of the contract into the lane's slot: snap,
+// bounding box inside the tile, edges.  Returns its number of jobs (0: covers
+// nothing here, or already drawn).  Where every triangle of the wave has a box
+// of at most kTinyArea pixels each lane walks its own; one larger box makes
+// the queue, whose setup all lanes run together, cheaper for all of them
+// (measured with 1 / 4 / 9 px: 1280x960 with 4 M triangles 9.31 / 8.83 / 8.73
+// ms a call, 9.32 without; ICP of 32 pairs of 320x240 297 us, 314 without;
+// 640x480 with 1 M triangles within 1.5 %).
+template <int TW>
+__device__ __forceinline__ int emit_tri(uint64_t* keys, WaveQueue& q, int lane, const float* rmin, const Tile& tl, const CamF& cam, float3 A, float3 B,
+                                        float3 C, const WPlane& pl, uint32_t id) {
+    int X[3], Y[3];
+    if (!snap(cam, A, X[0], Y[0]) || !snap(cam, B, X[1], Y[1]) || !snap(cam, C, X[2], Y[2])) return 0;
+    const int mnx = min(X[0], min(X[1], X[2])), mxx = max(X[0], max(X[1], X[2]));
+    const int mny = min(Y[0], min(Y[1], Y[2])), mxy = max(Y[0], max(Y[1], Y[2]));
+    // (a pixel centre on the triangle's lowest row is never covered)
+    const int px0 = max((mnx + 255) >> 8, tl.x0), px1 = min(mxx >> 8, tl.x1);
+    const int py0 = max((mny + 255) >> 8, tl.y0), py1 = min((mxy - 1) >> 8, tl.y1);
+    if (px0 > px1 || py0 > py1) return 0;
+    const int boxpx = (px1 - px0 + 1) * (min(mxy >> 8, tl.y1) - py0 + 1);
+    uint32_t box = (uint32_t)(px0 - tl.x0) | ((uint32_t)(px1 - tl.x0) << 6) | ((uint32_t)(py0 - tl.y0) << 12) |
+                   ((uint32_t)(py1 - tl.y0) << 18);
+    if (!__ballot(boxpx > kTinyArea || mxx - mnx >= (1 << 14) || mxy - mny >= (1 << 14))) {
+        raster_tiny(keys, TW + 1, rmin, tl, X, Y, px0, px1, py0, py1, pl, (double)cam.cx, (double)cam.cy, id);
+        return 0;
+    }
+    double pa = pl.a, pb = pl.b, w0 = fma(pl.a, (double)px0 - (double)cam.cx, pl.e);
+    if (boxpx <= kSmallArea && mxx - mnx < (1 << 14) && mxy - mny < (1 << 14)) {
+        box |= kSmallBox;
+        w0 = fma(pl.b, (double)py0 - (double)cam.cy, w0);
+        if (!exact_steps(w0, pa, pb, px1 - px0, py1 - py0)) box |= kStepBox;
+    }
+    const int ox = 256 * tl.x0, oy = 256 * tl.y0;
+    if (mnx - ox > -kSpanLimit && mxx - ox < kSpanLimit && mny - oy > -kSpanLimit && mxy - oy < kSpanLimit) {
+        auto order = [&](int i, int j) {           // Y[i] <= Y[j]
+            const bool s = Y[j] < Y[i];
+            const int x = X[i], y = Y[i];
+            X[i] = s ? X[j] : x; Y[i] = s ? Y[j] : y;
+            X[j] = s ? x : X[j]; Y[j] = s ? y : Y[j];
+        };
+        order(0, 1); order(1, 2); order(0, 1);
+        q.xa[lane] = fma((double)(X[0] - ox), 1.0 / 256.0, -kSpanTie);
+        q.xb[lane] = fma((double)(X[1] - ox), 1.0 / 256.0, -kSpanTie);
+        // (a horizontal edge's slope is never used: no row has YA <= y < YB = YA)
+        q.mac[lane] = div_int(X[2] - X[0], Y[2] - Y[0]) * (1.0 / 256.0);
+        q.mab[lane] = div_int(X[1] - X[0], Y[1] - Y[0]) * (1.0 / 256.0);
+        q.mbc[lane] = div_int(X[2] - X[1], Y[2] - Y[1]) * (1.0 / 256.0);
+        q.ya[lane] = Y[0] - oy;
+        q.yb[lane] = Y[1] - oy;
+    } else {
+        const int64_t area = (int64_t)(X[1] - X[0]) * (int64_t)(Y[2] - Y[0]) -
+                             (int64_t)(Y[1] - Y[0]) * (int64_t)(X[2] - X[0]);
+        if (area == 0) return 0;
+        if (area < 0) {
+            int t = X[1]; X[1] = X[2]; X[2] = t;
+            t = Y[1]; Y[1] = Y[2]; Y[2] = t;
+        }
+        q.xa[lane] = __hiloint2double(Y[0] - oy, X[0] - ox);
+        q.xb[lane] = __hiloint2double(Y[1] - oy, X[1] - ox);
+        q.mac[lane] = __hiloint2double(Y[2] - oy, X[2] - ox);
+        box |= kWideBox;
+    }
+    q.pa[lane] = pa; q.pb[lane] = pb; q.w0[lane] = w0;
+    q.id[lane] = id;
+    q.box[lane] = box;
+    return py1 - py0 + 1;
+}
 
-constexpr int kMaxBands = 16;             // tile height / kBand for the tallest tile (32 rows)
-static_assert(32 / kBand <= kMaxBands && kMaxBands <= 16, "job records hold a 4-bit band index");
-static_assert((kQCap << 4) + 15 <= 0xffff, "job records are 16-bit");
-static_assert(kSmallArea <= 64, "in-thread edge functions stay within int32 only for spans below 64 px");
-struct BigQueue {
-    int X[3][kQCap], Y[3][kQCap];          // snapped vertices relative to the tile origin (1/256 px)
-    double m[3][kQCap];                    // edge slope dx/dy (0 for horizontal edges)
-    double pa[kQCap], pb[kQCap], pe[kQCap];
-    uint32_t id[kQCap];
-    uint32_t box[kQCap];                   // tile-relative px0 | px1 << 8 | py0 << 16 | py1 << 24
-    uint16_t job[kQCap * kMaxBands];       // queued entry << 4 | band, only bands the entry covers
-    int n, njobs;
-};
-
-// Rows r0..r1 (tile-relative) of one sub-triangle with tile-relative snapped
-// vertices (X, Y), edge slopes m, depth plane and tile-relative column range.
-__device__ __forceinline__ void raster_rows(uint64_t* keys, int tile_w, const Tile& tl, const float* rmin,
-                                            const int X[3], const int Y[3], const double m[3], double pa, double pb,
-                                            double pe,
-                                            uint32_t id, int bx0, int bx1, int r0, int r1, double cx, double cy) {
-    int64_t E[3];
-    int dx[3], dy[3];
-    double xc[3];
+// Span [xa, xb] of row r of a triangle with far vertices inside its box columns:
+// int64 edge functions at every pixel (|products| < 2^61).
+__device__ __forceinline__ void wide_span(const WaveQueue& q, int o, int r, int bx0, int bx1, int& xa, int& xb) {
+    int64_t E[3], sx[3];
+    const double v[3] = {q.xa[o], q.xb[o], q.mac[o]};
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         const int k1 = k == 2 ? 0 : k + 1;
-        dx[k] = X[k1] - X[k];
-        dy[k] = Y[k1] - Y[k];
-        const bool topleft = dy[k] < 0 || (dy[k] == 0 && dx[k] > 0);
-        E[k] = (int64_t)dx[k] * (int64_t)(256 * r0 - Y[k]) - (int64_t)dy[k] * (int64_t)(256 * bx0 - X[k]) -
-               (topleft ? 0 : 1);
-        xc[k] = ((double)X[k] + (double)(256 * r0 - Y[k]) * m[k]) * (1.0 / 256.0);   // crossing on row r0
+        const int X = __double2loint(v[k]), Y = __double2hiint(v[k]);
+        const int dx = __double2loint(v[k1]) - X, dy = __double2hiint(v[k1]) - Y;
+        const bool topleft = dy < 0 || (dy == 0 && dx > 0);
+        E[k] = (int64_t)dx * (int64_t)(256 * r - Y) - (int64_t)dy * (int64_t)(256 * bx0 - X) - (topleft ? 0 : 1);
+        sx[k] = -256 * (int64_t)dy;
     }
-    double wrow = fma(pb, (double)(tl.y0 + r0) - cy, fma(pa, (double)(tl.x0 + bx0) - cx, pe));
-    for (int r = r0; r <= r1; ++r) {
-        double lo = (double)bx0, hi = (double)bx1;
-        bool empty = false;
-        // selects instead of branches: the three edges' cases differ per lane
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const double c = xc[k];
-            lo = ((dy[k] < 0) & (c > lo)) ? c : lo;
-            hi = ((dy[k] > 0) & (c < hi)) ? c : hi;
-            empty |= (dy[k] == 0) & (E[k] < 0);     // horizontal edge: the whole row is in or out
+    xa = bx1 + 1;
+    xb = bx0 - 1;
+#pragma unroll 1
+    for (int x = bx0; x <= bx1; ++x) {
+        if ((E[0] | E[1] | E[2]) >= 0) {
+            xa = min(xa, x);
+            xb = x;
         }
-        // lo >= bx0 and hi <= bx1 already; clamp the other side before converting
-        const int xa = max(bx0, (int)ceil(fmin(lo, (double)bx1 + 1.0) - 1e-6));
-        const int xb = min(bx1, (int)floor(fmax(hi, (double)bx0 - 1.0) + 1e-6));
-        double w = fma(pa, (double)(xa - bx0), wrow);
-        if (!empty && xa <= xb && fmax(w, fma(pa, (double)(xb - xa), w)) * kOccMargin >= (double)snap_min(rmin, r, xa, xb)) {
-            // The bracket's crossings are exact to far below a pixel, so a
-            // pixel centre one pixel or more inside it is covered: only its
-            // end pixels take the exact int64 edge test, and an end that
-            // fails it is left out of the span.
-            auto inside = [&](int x) {
-                const int64_t o = 256 * (int64_t)(x - bx0);
-                return ((E[0] - o * dy[0]) | (E[1] - o * dy[1]) | (E[2] - o * dy[2])) >= 0;
-            };
-            const bool in_a = inside(xa), in_b = inside(xb);
-            if (!in_a) w += pa;                // the span's first pixel, accumulated as before
-            uint64_t* row = keys + r * tile_w;
-            for (uint64_t *k = row + xa + (in_a ? 0 : 1), *kend = row + xb - (in_b ? 0 : 1); k <= kend; ++k) {
-                atomicMax((unsigned long long*)k, pack_key((float)w, id));
-                w += pa;
+        E[0] += sx[0]; E[1] += sx[1]; E[2] += sx[2];
+    }
+}
+
+// Deals the wave's jobs out to its lanes, 64 at a time.  nj: the jobs of the
+// lane's own triangle.
+template <int TW>
+__device__ __forceinline__ void raster_jobs(uint64_t* keys, WaveQueue& q, const Tile& tl, const float* rmin, int lane,
+                                            int nj, double cy) {
+    const int end = wave_scan_add(nj);
+    const int total = __builtin_amdgcn_readlane(end, 63);
+    const int base = end - nj;
+    q.base[lane] = base;
+    for (int s = 0; s < total; s += 64) {
+        // the owner of a job is the last lane whose first job is at or before it
+        q.slot[lane] = 0;
+        wave_lds_sync();
+        if (nj > 0 && base < s + 64 && end > s) q.slot[max(base - s, 0)] = lane + 1;
+        wave_lds_sync();
+        const int o = wave_scan_max(q.slot[lane]) - 1;
+        const int j = s + lane;
+        if (j < total) {
+            // (one straight line of code up to the rare cases: the slot's
+            // loads overlap)
+            const uint32_t box = q.box[o];
+            const uint32_t id = q.id[o];
+            const int y0 = q.base[o], ya = q.ya[o], yb = q.yb[o];
+            const double pa = q.pa[o], pb = q.pb[o], w0 = q.w0[o];
+            const double XA = q.xa[o], XB = q.xb[o], mac = q.mac[o], mab = q.mab[o], mbc = q.mbc[o];
+            const int bx0 = box & 63, bx1 = (box >> 6) & 63, by0 = (box >> 12) & 31;
+            const int r = by0 + j - y0, y = 256 * r;
+            const bool small = (box & kSmallBox) != 0;
+            const double v = (double)(small ? r - by0 : tl.y0 + max(by0, r & ~1)) - (small ? 0.0 : cy);
+            const double we = fma(pb, v, w0), wo = we + pb;
+            const double wrow = !small && (r & 1) && r > by0 ? wo : we;
+            const double cl = fma((double)(y - ya), mac, XA);
+            const double c1 = fma((double)(y - ya), mab, XA), c2 = fma((double)(y - yb), mbc, XB);
+            const double cs = y < yb ? c1 : c2;
+            int xa = max(bx0, (int)ceil(fmin(cl, cs)));
+            int xb = min(bx1, (int)ceil(fmax(cl, cs)) - 1);
+            if (__builtin_expect((box & kWideBox) != 0, 0)) wide_span(q, o, r, bx0, bx1, xa, xb);
+            double w = fma(pa, (double)(xa - bx0), wrow), wt = small ? wrow : w;
+            if (__builtin_expect((box & kStepBox) != 0, 0)) {
+                w = w0;
+#pragma unroll 1
+                for (int k = by0; k < r; ++k) w += pb;
+                wt = w;
+#pragma unroll 1
+                for (int k = bx0; k < xa; ++k) w += pa;
+            }
+            // the row's nearest depth, over its span or a small triangle's box
+            // columns, behind everything visible there changes no key
+            const int sa = small ? bx0 : xa, sb = small ? bx1 : xb;
+            uint64_t* row = keys + r * (TW + 1);
+            if (xa <= xb && fmax(wt, fma(pa, (double)(sb - sa), wt)) * kOccMargin >= (double)snap_min(rmin, r, sa, sb)) {
+                // (the loop runs on the key address; the far plane is applied
+                // at the resolve, see there)
+                for (uint64_t *k = row + xa, *kend = row + xb; k <= kend; ++k) {
+                    atomicMax((unsigned long long*)k, pack_key((float)w, id));
+                    w += pa;
+                }
             }
         }
-#pragma unroll
-        for (int k = 0; k < 3; ++k) { E[k] += 256 * (int64_t)dx[k]; xc[k] += m[k]; }
-        wrow += pb;
+        wave_lds_sync();
     }
-}
-
-template <int TW, int TH>
-__device__ __forceinline__ void raster_queue(uint64_t* keys, BigQueue& q, const Tile& tl, const float* rmin,
-                                             double cx, double cy) {
-    const int nj = q.njobs;
-    for (int j = threadIdx.x; j < nj; j += kWG) {
-        const int rec = q.job[j];
-        const int b = rec >> 4, band = rec & 15;
-        const uint32_t box = q.box[b];
-        const int by0 = (int)((box >> 16) & 0xff), by1 = (int)(box >> 24);
-        const int r0 = max(by0, band * kBand), r1 = min(by1, band * kBand + kBand - 1);
-        const int X[3] = {q.X[0][b], q.X[1][b], q.X[2][b]};
-        const int Y[3] = {q.Y[0][b], q.Y[1][b], q.Y[2][b]};
-        const double m[3] = {q.m[0][b], q.m[1][b], q.m[2][b]};
-        raster_rows(keys, TW, tl, rmin, X, Y, m, q.pa[b], q.pb[b], q.pe[b], q.id[b], (int)(box & 0xff),
-                    (int)((box >> 8) & 0xff), r0, r1, cx, cy);
-    }
-}
-
-// Setup of one (sub-)triangle of the contract: snap, orientation, bounding
-// box inside the tile, then the rasterization path by size.
-struct Queues {
-    BigQueue big;
-    // per kSeg-pixel segment of each tile row, the farthest w = 1/z held by
-    // its keys (0 if a pixel is empty) at the start of the round, and at
-    // kSnapTile the tile's farthest; two buffers, one filled per round
-    float rowmin[2][kSnapTile + 1];
-};
-
-__device__ __forceinline__ bool emit_tri(uint64_t* keys, int tile_w, Queues& Q, const float* rmin, const Tile& tl,
-                                         const CamF& cam, float3 A, float3 B, float3 C, const WPlane& pl,
-                                         uint32_t id) {
-    int X[3], Y[3];
-    if (!snap(cam, A, X[0], Y[0]) || !snap(cam, B, X[1], Y[1]) || !snap(cam, C, X[2], Y[2])) return true;
-    const int64_t area = (int64_t)(X[1] - X[0]) * (int64_t)(Y[2] - Y[0]) -
-                         (int64_t)(Y[1] - Y[0]) * (int64_t)(X[2] - X[0]);
-    if (area == 0) return true;
-    if (area < 0) {
-        int t = X[1]; X[1] = X[2]; X[2] = t;
-        t = Y[1]; Y[1] = Y[2]; Y[2] = t;
-    }
-    const int mnx = min(X[0], min(X[1], X[2])), mxx = max(X[0], max(X[1], X[2]));
-    const int mny = min(Y[0], min(Y[1], Y[2])), mxy = max(Y[0], max(Y[1], Y[2]));
-    const int px0 = max((mnx + 255) >> 8, tl.x0), px1 = min(mxx >> 8, tl.x1);
-    const int py0 = max((mny + 255) >> 8, tl.y0), py1 = min(mxy >> 8, tl.y1);
-    if (px0 > px1 || py0 > py1) return true;
-    const int boxpx = (px1 - px0 + 1) * (py1 - py0 + 1);
-    const uint32_t box = (uint32_t)(px0 - tl.x0) | ((uint32_t)(px1 - tl.x0) << 8) | ((uint32_t)(py0 - tl.y0) << 16) |
-                         ((uint32_t)(py1 - tl.y0) << 24);
-    if (boxpx <= kSmallArea && mxx - mnx < (1 << 14) && mxy - mny < (1 << 14)) {
-        raster_small(keys, tile_w, tl, rmin, X, Y, px0, px1, py0, py1, pl, (double)cam.cx, (double)cam.cy, id);
-        return true;
-    }
-    const int k = atomicAdd(&Q.big.n, 1);
-    if (k >= kQCap) return false;              // queue full: queued again in another pass of the round
-    int Xr[3], Yr[3];
-    double m[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const int i1 = i == 2 ? 0 : i + 1;
-        const int dx = X[i1] - X[i], dy = Y[i1] - Y[i];
-        Xr[i] = X[i] - 256 * tl.x0;
-        Yr[i] = Y[i] - 256 * tl.y0;
-        m[i] = dy != 0 ? (double)dx / (double)dy : 0.0;
-    }
-#pragma unroll
-    for (int i = 0; i < 3; ++i) { Q.big.X[i][k] = Xr[i]; Q.big.Y[i][k] = Yr[i]; Q.big.m[i][k] = m[i]; }
-    Q.big.pa[k] = pl.a; Q.big.pb[k] = pl.b; Q.big.pe[k] = pl.e;
-    Q.big.id[k] = id;
-    Q.big.box[k] = box;
-    const int b0 = (py0 - tl.y0) / kBand, b1 = (py1 - tl.y0) / kBand;
-    const int j0 = atomicAdd(&Q.big.njobs, b1 - b0 + 1);
-    for (int b = b0; b <= b1; ++b) Q.big.job[j0 + b - b0] = (uint16_t)((k << 4) | b);
-    return true;
 }
 
 __device__ __forceinline__ float3 sel3(int k, float3 a, float3 b, float3 c) {
@@ -379,13 +513,14 @@ __device__ __forceinline__ void load_vertices(const float* __restrict__ xyz, int
 }
 
 // Whole contract for one mesh triangle: transform, far cull, near clip into
-// at most two sub-triangles (same id), setup and rasterization.  Sub-triangle
-// k is left out where bit k of skip is set; returns the mask of the
-// sub-triangles that found the band queue full (0: the triangle is done).
-template <int MODE>
-__device__ __forceinline__ int raster_triangle(uint64_t* keys, int tile_w, Queues& q, const float* rmin,
-                                               const Tile& tl, const CamF& cam, double ifx, double ify,
-                                               const PoseF& P, const TriIn& in, int skip) {
+// at most two sub-triangles (same id), and the setup of sub-triangle `sub` in
+// the lane's queue slot.  Returns the sub-triangle's jobs; *two is set where
+// the triangle has a second one.
+template <int MODE, int TW>
+__device__ __forceinline__ int setup_triangle(uint64_t* keys, WaveQueue& q, int lane, const float* rmin, const Tile& tl,
+                                              const CamF& cam, double ifx, double ify, const PoseF& P,
+                                              const TriIn& in, int sub, bool* two) {
+    *two = false;
     const float x0 = in.v[0], y0 = in.v[1], z0 = in.v[2];
     const float3 V0 = cam_contract(P, x0, y0, z0);
     const float3 V1 = cam_contract(P, in.v[3], in.v[4], in.v[5]);
@@ -402,37 +537,37 @@ __device__ __forceinline__ int raster_triangle(uint64_t* keys, int tile_w, Queue
     // taken multiplied by z_min |c| > 0, so that a skipped triangle needs no
     // division (c = 0, a plane through the camera centre, is never skipped);
     // in ICP mode the plane first (fewer registers live across the test there).
+    const float wt = fminf(fminf(rmin[kSnapTile], rmin[kSnapTile + 1]), fminf(rmin[kSnapTile + 2], rmin[kSnapTile + 3]));
     WPlane pl;
     if constexpr (MODE == kIcp) {
         pl = depth_plane(pn, ifx, ify);
         if (nin == 3) {
             const double wv = 1.0 / (double)fminf(V0.z, fminf(V1.z, V2.z)) + fabs(pl.a) + fabs(pl.b);
-            if (wv * 1.00001 < (double)rmin[kSnapTile]) return 0;
+            if (wv * 1.00001 < (double)wt) return 0;
         }
     } else {
         if (nin == 3) {
             const double zmin = (double)fminf(V0.z, fminf(V1.z, V2.z));
             const double ac = fabs(pn.c);
             const double lhs = (ac + zmin * (fabs(pn.nx) * ifx + fabs(pn.ny) * ify)) * 1.00001;
-            if (lhs < (double)rmin[kSnapTile] * zmin * ac) return 0;
+            if (lhs < (double)wt * zmin * ac) return 0;
         }
         pl = depth_plane(pn, ifx, ify);
     }
     const uint32_t id = (uint32_t)in.t;
     // near-plane clip into at most two sub-triangles; one emit call site keeps
-    // a single copy of the setup and rasterization code
-    float3 A0 = V0, B0 = V1, C0 = V2, A1 = V0, B1 = V1, C1 = V2;
-    int nsub = 1;
+    // a single copy of the setup code
+    float3 A0 = V0, B0 = V1, C0 = V2;
     if (nin == 2) {
         const int k = !in0 ? 0 : (!in1 ? 1 : 2);          // the outside vertex
         const float3 O = sel3(k, V0, V1, V2);
         const float3 a = sel3(k == 2 ? 0 : k + 1, V0, V1, V2);
         const float3 b = sel3(k == 0 ? 2 : k - 1, V0, V1, V2);
         const float3 Pb = clip_point(b, O, cam.zn);
-        const float3 Pa = clip_point(a, O, cam.zn);
-        A0 = a; B0 = b; C0 = Pb;
-        A1 = a; B1 = Pb; C1 = Pa;
-        nsub = 2;
+        *two = true;
+        A0 = a;
+        if (sub) { B0 = Pb; C0 = clip_point(a, O, cam.zn); }
+        else { B0 = b; C0 = Pb; }
     } else if (nin == 1) {
         const int k = in0 ? 0 : (in1 ? 1 : 2);            // the inside vertex
         const float3 I = sel3(k, V0, V1, V2);
@@ -440,14 +575,7 @@ __device__ __forceinline__ int raster_triangle(uint64_t* keys, int tile_w, Queue
         const float3 b = sel3(k == 0 ? 2 : k - 1, V0, V1, V2);
         A0 = I; B0 = clip_point(I, a, cam.zn); C0 = clip_point(I, b, cam.zn);
     }
-    int left = 0;
-#pragma unroll 1
-    for (int sub = 0; sub < nsub; ++sub) {
-        if ((skip >> sub) & 1) continue;
-        const float3 A = sub ? A1 : A0, B = sub ? B1 : B0, C = sub ? C1 : C0;
-        if (!emit_tri(keys, tile_w, q, rmin, tl, cam, A, B, C, pl, id)) left |= 1 << sub;
-    }
-    return left;
+    return emit_tri<TW>(keys, q, lane, rmin, tl, cam, A0, B0, C0, pl, id);
 }
 
 // ------------------------------------------------------------------ binning
@@ -978,14 +1106,6 @@ __device__ __forceinline__ void decode_rec(const BatchDesc& bd, int64_t rec, Ite
     it.rec = rec;
 }
 
-// A pointer whose value is the same in every lane, moved to scalar registers.
-__device__ __forceinline__ const uint32_t* uniform_ptr(const uint32_t* p) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return reinterpret_cast<const uint32_t*>((uint64_t)hi << 32 | lo);
-}
-
 // Sums of N values per lane over the 64 lanes of a wave: row r of 16 lanes
 // ends with the sum of v[4 k + (r >> 1 | (r & 1) << 1)] in out[k].  Every sum is the
 // tree that pairs lanes 32, 16, 8, 4, 2 and 1 apart, in that order.  The first
@@ -1020,7 +1140,12 @@ __device__ __forceinline__ void wave_sums(const T (&v)[N], T (&out)[K]) {
             swap_add16(swap_add32(at(4 * k), at(4 * k + 1)), swap_add32(at(4 * k + 2), at(4 * k + 3)))))));
 }
 
-// One (scan, pose, tile) item: rasterization rounds, resolve, tile record.
+// Keys of a tile in LDS: rows of TW + 1, so that the rows of one column lie in
+// different banks.
+template <int TW, int TH>
+constexpr int kKeys = (TW + 1) * TH;
+
+// One (scan, pose, tile) item: rasterization, resolve, tile record.
 template <int TW, int TH, int MODE, bool OVF>
 __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs& a, const ItemInfo& it,
                                           uint64_t* keys, Queues& q, float (*red)[kRecFields]) {
@@ -1028,7 +1153,7 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
     CamF cam{sd.fx, sd.fy, sd.cx, sd.cy, sd.z_near, sd.z_far, sd.width, sd.height};
     const float ifx = 1.0f / cam.fx, ify = 1.0f / cam.fy;
     const double difx = (double)ifx, dify = (double)ify;
-    const double dcx = (double)cam.cx, dcy = (double)cam.cy;
+    const double dcy = (double)cam.cy;
     const float w_far = 1.0f / cam.zf;
     const int tx = it.tile % sd.tiles_x, ty = it.tile / sd.tiles_x;
     Tile tl;
@@ -1036,10 +1161,14 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
     tl.x1 = min(tl.x0 + TW, cam.W) - 1; tl.y1 = min(tl.y0 + TH, cam.H) - 1;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
-    for (int p = tid; p < TW * TH; p += kWG) keys[p] = kEmptyKey;
+    for (int p = tid; p < kKeys<TW, TH>; p += kWG) keys[p] = kEmptyKey;
 
     PoseF P;
     load_pose(a.T_wc + 12 * (int64_t)it.pose, P);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) P.R[i][j] = uniform(P.R[i][j]);
     const int ns = a.bin_small[it.rec], nb = a.bin_big[it.rec];
     if (tid < 2) atomicMax(a.bin_max + tid, tid ? nb : ns);    // one instruction, two lanes
 
@@ -1057,10 +1186,8 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
     const bool use_bin = fits || poff >= 0;
     const int nvis = a.vis_count[it.pose];
     const uint2* vis = a.vis + (int64_t)it.pose * a.n_clusters;
-    // (uniform over the workgroup: kept in scalar registers for the gather)
-    const uint32_t* bin = OVF ? uniform_ptr(poff >= 0 ? a.pool + poff : a.bins + it.rec * (int64_t)a.bin_cap)
-                              : a.bins + it.rec * (int64_t)a.bin_cap;
-    const int bcap = OVF ? __builtin_amdgcn_readfirstlane(poff >= 0 ? ns + nb : a.bin_cap) : a.bin_cap;
+    const uint32_t* bin = OVF && poff >= 0 ? a.pool + poff : a.bins + it.rec * (int64_t)a.bin_cap;
+    const int bcap = OVF && poff >= 0 ? ns + nb : a.bin_cap;
     const int nr = use_bin ? (ns + nb + kWG - 1) / kWG : nvis;
     auto entry = [&](int r) -> int32_t {
         if (r >= nr) return -1;
@@ -1072,83 +1199,66 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
         const int64_t t = (int64_t)vis[r].x * kClusterTris + tid;
         return t < a.n_tris ? (int32_t)t : -1;
     };
-    // three-stage gather pipeline: round r processes vertices loaded during
-    // round r-1 from indices loaded during r-2 from a bin entry read in r-3
-    TriIn cur, nxt;
-    uint32_t I1[3], I2[3];
-    int32_t t1 = entry(0), t2, t3;
+    // gather pipeline: the vertices of chunk r are loaded while chunk r - 1 is
+    // rasterized, from indices loaded during r - 2 and a bin entry read in r - 3
+    TriIn cur;
+    uint32_t I1[3];
+    int32_t t1 = entry(0), t2;
     load_indices(a.tri, a.vmax, t1, I1);
     load_vertices(a.xyz, t1, I1, cur);
     t1 = entry(1);
     load_indices(a.tri, a.vmax, t1, I1);
     t2 = entry(2);
-    // The snapshot is refreshed after each of the first kSnapEvery rounds and
-    // then after every kSnapEvery-th: the near surfaces arrive first, and an
-    // older snapshot stays a valid bound (keys only move nearer), so later
-    // rounds cull almost as well at a fraction of the cost.  Buffer cb is
-    // read by the current round; a refresh fills the other and swaps.
-    if (tid <= kSnapTile) q.rowmin[0][tid] = 0.0f;   // round 0 sees an empty buffer
-    int cb = 0;
+    // Each wave refreshes its quarter of the snapshot after each of its first
+    // kSnapEvery chunks and then after every kSnapEvery-th: the near surfaces
+    // arrive first, and an older snapshot stays a valid bound (keys only move
+    // nearer), so later chunks cull almost as well at a fraction of the cost.
+    if (tid < kSnapTile + kWaves) q.rowmin[tid] = 0.0f;
+    WaveQueue& wq = q.w[wave];
+    __syncthreads();                           // keys and snapshot are initialized
     for (int r = 0; r < nr; ++r) {
-        const bool snap_now = r + 1 < nr && (r < kSnapEvery || r % kSnapEvery == 0);
-        if (tid == 0) { q.big.n = 0; q.big.njobs = 0; }
-        if (tid == 0 && snap_now) q.rowmin[cb ^ 1][kSnapTile] = __int_as_float(0x7f800000);
-        const float* rmin = q.rowmin[cb];
-        load_vertices(a.xyz, t1, I1, nxt);
-        load_indices(a.tri, a.vmax, t2, I2);
-        t3 = entry(r + 3);
-        __syncthreads();
-        // A sub-triangle that finds the band queue full is queued in another
-        // pass once the queue has been drained; only its triangle id and the
-        // mask of pending sub-triangles stay live, its inputs are gathered
-        // again (only rounds with more large sub-triangles than the queue
-        // holds, mostly a bin's first rounds, take further passes).
-        int left = cur.t >= 0 ? raster_triangle<MODE>(keys, TW, q, rmin, tl, cam, difx, dify, P, cur, 0) : 0;
-        int32_t t_left = left ? cur.t : -1;
-        for (;;) {
-            __syncthreads();
-            const bool more = q.big.n > kQCap;   // some sub-triangle found the queue full
-            if (q.big.njobs) raster_queue<TW, TH>(keys, q.big, tl, rmin, dcx, dcy);
-            __syncthreads();
-            if (!more) break;
-            if (tid == 0) { q.big.n = 0; q.big.njobs = 0; }
-            __syncthreads();
-            if (t_left >= 0) {
+        bool two = false;
+        int nj = cur.t >= 0 ? setup_triangle<MODE, TW>(keys, wq, lane, q.rowmin, tl, cam, difx, dify, P, cur, 0, &two) : 0;
+        const int32_t tc = cur.t;
+        load_vertices(a.xyz, t1, I1, cur);
+        t1 = t2;
+        load_indices(a.tri, a.vmax, t1, I1);
+        t2 = entry(r + 3);
+        raster_jobs<TW>(keys, wq, tl, q.rowmin, lane, nj, dcy);
+        // second sub-triangles of triangles clipped at the near plane (rare):
+        // their inputs are gathered again, so that they need not stay live
+        if (__ballot(two)) {
+            nj = 0;
+            if (two) {
                 TriIn tri;
                 uint32_t I[3];
-                load_indices(a.tri, a.vmax, t_left, I);
-                load_vertices(a.xyz, t_left, I, tri);
-                left = raster_triangle<MODE>(keys, TW, q, rmin, tl, cam, difx, dify, P, tri, ~left & 3);
-                if (!left) t_left = -1;
+                load_indices(a.tri, a.vmax, tc, I);
+                load_vertices(a.xyz, tc, I, tri);
+                nj = setup_triangle<MODE, TW>(keys, wq, lane, q.rowmin, tl, cam, difx, dify, P, tri, 1, &two);
             }
+            raster_jobs<TW>(keys, wq, tl, q.rowmin, lane, nj, dcy);
         }
-        // row and tile snapshot for the next round (w >= 0, so its bits order
-        // like its value).  Pixel p = tid + k kWG lies in row p / TW, so the
-        // kG lanes of a group cover one kSeg-pixel segment (or, for 8-pixel
-        // tile rows, one row): a group minimum and one store per segment;
-        // the tile's farthest is a wave minimum and one atomic per wave.
-        if (snap_now) {
+        // segment and quarter minimums (w >= 0, so its bits order like its
+        // value): the kG lanes of a group cover one kSeg-pixel segment (or,
+        // for 8-pixel tile rows, one row)
+        if (r + 1 < nr && (r < kSnapEvery || r % kSnapEvery == 0)) {
             constexpr int kG = TW < kSeg ? TW : kSeg;
-            float* snap = q.rowmin[cb ^ 1];
+            constexpr int kPer = TW * TH / kWaves;         // pixels of a wave's quarter
             uint32_t tmin = 0x7f800000u;
-            for (int p = tid; p < TW * TH; p += kWG) {
-                const uint32_t wb = group_min<kG>((uint32_t)(keys[p] >> 32));
-                if ((lane & (kG - 1)) == 0) snap[(p / TW) * kSegs + (p % TW) / kSeg] = __uint_as_float(wb);
+#pragma unroll
+            for (int k = 0; k < (kPer + 63) / 64; ++k) {
+                const int i = k * 64 + lane, p = wave * kPer + min(i, kPer - 1);
+                const uint32_t wb = group_min<kG>((uint32_t)(keys[(p / TW) * (TW + 1) + p % TW] >> 32));
+                if (i < kPer && (lane & (kG - 1)) == 0) q.rowmin[(p / TW) * kSegs + (p % TW) / kSeg] = __uint_as_float(wb);
                 tmin = min(tmin, wb);
             }
-            if (tid < TW * TH) {
-                tmin = min(tmin, (uint32_t)__shfl_xor((int)tmin, 16));
-                tmin = min(tmin, (uint32_t)__shfl_xor((int)tmin, 32));
-                if constexpr (kG == 8) tmin = min(tmin, (uint32_t)__shfl_xor((int)tmin, 8));
-                if (lane == 0) atomicMin((unsigned int*)&snap[kSnapTile], tmin);
-            }
+            if constexpr (kG == 8) tmin = min(tmin, (uint32_t)__shfl_xor((int)tmin, 8));
+            tmin = min(tmin, (uint32_t)__shfl_xor((int)tmin, 16));
+            tmin = min(tmin, (uint32_t)__shfl_xor((int)tmin, 32));
+            if (lane == 0) q.rowmin[kSnapTile + wave] = __uint_as_float(tmin);
         }
-        if (snap_now) cb ^= 1;
-        cur = nxt;
-        t1 = t2;
-        I1[0] = I2[0]; I1[1] = I2[1]; I1[2] = I2[2];
-        t2 = t3;
     }
+    __syncthreads();                           // every wave's keys are in
 
     // ---------------------------------------------------------------- resolve
     Acc acc;
@@ -1169,7 +1279,7 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
     for (int p = tid; p < TW * TH; p += kWG) {
         const int x = tl.x0 + p % TW, y = tl.y0 + p / TW;
         if (x > tl.x1 || y > tl.y1) continue;
-        const uint64_t key = keys[(y - tl.y0) * TW + (x - tl.x0)];
+        const uint64_t key = keys[(y - tl.y0) * (TW + 1) + (x - tl.x0)];
         // The rasterizers offer fragments beyond the far plane too (w below
         // w_far); such a fragment is farther than any valid one, so it is
         // the pixel's key only where no valid fragment exists, and a key
@@ -1355,7 +1465,7 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
 // reaches that exit.
 template <int TW, int TH, int MODE, bool OVF>
 __global__ void __launch_bounds__(kWG, 4) k_raster(BatchDesc bd, RasterArgs a) {
-    __shared__ uint64_t keys[TW * TH];
+    __shared__ uint64_t keys[kKeys<TW, TH>];
     __shared__ Queues q;
     __shared__ float red[kWG / 64][kRecFields];
     if (!a.order) {
@@ -1369,7 +1479,7 @@ __global__ void __launch_bounds__(kWG, 4) k_raster(BatchDesc bd, RasterArgs a) {
         __syncthreads();                       // the previous item's shared data is no longer read
         if (threadIdx.x == 0) slot = atomicAdd(a.queue, 1);
         __syncthreads();
-        const int k = slot;
+        const int k = uniform(slot);
         if (k >= a.n_order) return;
         ItemInfo it;
         decode_rec(bd, a.order[k], it);
