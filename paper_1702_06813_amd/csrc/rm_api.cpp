@@ -366,6 +366,8 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
     int32_t* vis_tris = nullptr;
     int32_t* bin_max = nullptr;
     int64_t cap = 0, cap_b = 0;
+    // slices of split records
+    int64_t split_want = persistent && R <= kSplitRecords ? std::min<int64_t>(kMaxSplit, R * kMaxSlices) : 0;
     for (int attempt = 0;; ++attempt) {
         // the capacity learned so far (or fixed), limited to what this call's records may take
         cap = call_cap(ctx, R);
@@ -377,10 +379,12 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
         // the spilling kernel also measures what overflow must hold: always in a sizing pass
         const bool track = !arena.fixed && (check || ctx->pool_mode > 0 || shape_track);
         Carve cv;
-        // vis_count, vis_tris, bin_max[2], bin_fill[2], bin fills, order histogram and cursors, queue
-        const int64_t n_cnt = 2 * (int64_t)P + 4 + 2 * R + 65;
+        int64_t n_split = split_want;
+        // vis_count, vis_tris, bin_max[2], bin_fill[2], bin fills, order histogram and cursors, queue[2]
+        const int64_t n_cnt = 2 * (int64_t)P + 4 + 2 * R + kOrderWords;
         const size_t o_cnt = cv.take<int32_t>(n_cnt);
         const size_t o_ord = cv.take<int32_t>(persistent ? R : 1);
+        const size_t o_split = cv.take<uint4>(n_split);
         const size_t o_vis = cv.take<uint2>((int64_t)P * C);
         const size_t o_visz = cv.take<float>((int64_t)P * C);
         const size_t o_rec = cv.take<float>(mode == kRender ? 1 : R * kRecFields);
@@ -399,18 +403,27 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
         if (arena.fixed) {
             // bins take what the fixed buffer leaves; a bin that overflows a
             // smaller capacity is rasterized from every visible cluster (same result)
+            if (o_bin + 256 > arena.fixed_size && split_want > 0) {
+                split_want = 0;                // a call that fits without slices runs without
+                continue;
+            }
             if (o_bin + 256 > arena.fixed_size)
                 return fail(ctx, RM_ERR_CAPACITY, "the call needs %zu bytes of scratch besides its bins; the "
                                                   "allocation-free buffer holds %zu", o_bin + 256, arena.fixed_size);
             cap = std::min<int64_t>(cap, (int64_t)((arena.fixed_size - o_bin) / 4) / std::max<int64_t>(R, 1));
             cv.take<uint32_t>(R * cap);
+            // slots for split records from what is then left
+            n_split = std::min<int64_t>(n_split, (int64_t)((arena.fixed_size - std::min(arena.fixed_size, cv.off)) /
+                                                           ((size_t)tw * th * sizeof(uint64_t))));
             base = arena.fixed;
         } else {
             cv.take<uint32_t>(R * cap);
+            cv.take<uint64_t>(n_split * tw * th);
             int rc = ensure_scratch(ctx, cv.off);
             if (rc) return rc;
             base = static_cast<char*>(ctx->scratch);
         }
+        const size_t o_keys = o_bin + (((size_t)std::max<int64_t>(R * cap, 1) * sizeof(uint32_t) + 255) & ~(size_t)255);
         cap_b = big_part(ctx, cap);
         auto at = [&](size_t off) { return base + off; };
         vis_count = reinterpret_cast<int32_t*>(at(o_cnt));
@@ -465,6 +478,9 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
         a.order = nullptr;
         a.queue = hist + 64;
         a.n_order = (int32_t)R;
+        a.split = reinterpret_cast<uint4*>(at(o_split));
+        a.split_cap = (int32_t)n_split;
+        a.split_keys = reinterpret_cast<uint64_t*>(at(o_keys));
         a.rec = reinterpret_cast<float*>(at(o_rec));
         a.eps = eps;
         a.vnrm = vnrm;
@@ -481,7 +497,7 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
         if (be1) RM_HIP(ctx, hipEventRecord(be1, ctx->stream));
         if (persistent) {
             int32_t* order = reinterpret_cast<int32_t*>(at(o_ord));
-            RM_HIP(ctx, launch_order(ctx->stream, bd, bin_small, bin_big, R, hist, order));
+            RM_HIP(ctx, launch_order(ctx->stream, bd, a, R, hist, order, reinterpret_cast<uint4*>(at(o_split)), mode));
             a.order = order;
         }
         if (!check) break;
@@ -545,19 +561,17 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
     }
     RM_HIP(ctx, launch_raster(ctx->stream, bd, a, mode));
     if (pe1) RM_HIP(ctx, hipEventRecord(pe1, ctx->stream));
-    if (mode != kRender)
-        RM_HIP(ctx, launch_reduce(ctx->stream, bd, a.rec, vis_tris, eps, mode, out));
-    if (!capturing(ctx) && !ctx->bin_pending && !arena.fixed) {
+    const bool readback = !capturing(ctx) && !ctx->bin_pending && !arena.fixed;
+    Readback rb;
+    if (readback) {
+        rb.host = ctx->pinned;
+        rb.bin_max = bin_max;
+        rb.spill_top = a.spill_top;
+    }
+    if (mode != kRender) RM_HIP(ctx, launch_reduce(ctx->stream, bd, a.rec, vis_tris, eps, mode, out, rb));
+    else if (readback) RM_HIP(ctx, launch_read_back(ctx->stream, rb));
+    if (readback) {
         if (!ctx->bin_ev) RM_HIP(ctx, hipEventCreateWithFlags(&ctx->bin_ev, hipEventDisableTiming));
-        RM_HIP(ctx, hipMemcpyAsync(ctx->pinned + 1, bin_max, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
-        RM_HIP(ctx, hipMemcpyAsync(ctx->pinned + 4, bin_max + 1, sizeof(int32_t), hipMemcpyDeviceToHost,
-                                   ctx->stream));
-        if (a.spill_top) {
-            RM_HIP(ctx, hipMemcpyAsync(ctx->pinned + 6, a.spill_top, sizeof(int64_t), hipMemcpyDeviceToHost,
-                                       ctx->stream));
-            RM_HIP(ctx, hipMemcpyAsync(ctx->pinned + 12, a.spill_top + 4, sizeof(int64_t), hipMemcpyDeviceToHost,
-                                       ctx->stream));
-        }
         RM_HIP(ctx, hipEventRecord(ctx->bin_ev, ctx->stream));
         ctx->bin_pending = true;
         ctx->pool_pending = a.spill_top != nullptr;

@@ -92,9 +92,14 @@ struct RasterArgs {
     uint32_t* pool;              // [pool_cap] overflow regions
     int64_t pool_cap;
     int64_t* pool_off;           // [n_records] start of the record's region, -1: none
-    const int32_t* order;        // null: one workgroup per item; else record indices, longest first
-    int32_t* queue;              // device counter of taken items (persistent scheduling)
+    const int32_t* order;        // null: one workgroup per item; else record indices, longest first (-1: split)
+    int32_t* queue;              // device [2]: taken items, slices of split records (persistent scheduling)
     int32_t n_order;
+    // Records with many more triangles than a workgroup's share are rasterized
+    // by several workgroups, slice by slice; they come before the order.
+    const uint4* split;          // [split_cap] (record, slice, slices, first slice's slot), record -1: none
+    int32_t split_cap;           // 0: no record is split
+    uint64_t* split_keys;        // [split_cap][tile_w * tile_h] depth keys of each slice
     float* rec;                  // partial records [n_records][kRecFields]
     float eps;                   // Table I threshold; the association tolerance in ICP mode
     const float* vnrm;           // ICP mode: [n_vertices][3] world-frame vertex normals
@@ -129,13 +134,26 @@ hipError_t launch_bin(hipStream_t st, const BatchDesc& bd, const RasterArgs& a);
 hipError_t launch_overflow(hipStream_t st, const RasterArgs& a, int64_t n_records);
 hipError_t launch_raster(hipStream_t st, const BatchDesc& bd, const RasterArgs& a, int mode);
 // Longest-first order of the records of a binned call: counting sort of the
-// records by log2 of their bin fill, descending.  hist: 32 zeroed counters.
-hipError_t launch_order(hipStream_t st, const BatchDesc& bd, const int32_t* bin_small, const int32_t* bin_big,
-                        int64_t n_records, int32_t* hist, int32_t* order);
+// records by log2 of their bin fill, descending, after the slices of the
+// records it splits (a.split, a.queue[1]).  hist: kOrderWords zeroed words.
+constexpr int kOrderWords = 66;
+constexpr int kMaxSplit = 4096;          // slices of a call
+constexpr int kMaxSlices = 64;           // slices of a record
+constexpr int64_t kSplitRecords = 8192;  // calls with more records are not split
+hipError_t launch_order(hipStream_t st, const BatchDesc& bd, const RasterArgs& a, int64_t n_records, int32_t* hist,
+                        int32_t* order, uint4* split, int mode);
 // Workgroups of the persistent rasterizer that fit on the device at once.
 int persistent_grid(int tile_w, int tile_h, int mode);
-hipError_t launch_reduce(hipStream_t st, const BatchDesc& bd, const float* rec,
-                         const int32_t* vis_tris, float eps, int mode, double* out);
+// What later calls size their bins by, written at the end of a call (host ==
+// null: not read back).
+struct Readback {
+    int32_t* host = nullptr;             // pinned words, see rm_api.cpp
+    const int32_t* bin_max = nullptr;
+    const unsigned long long* spill_top = nullptr;
+};
+hipError_t launch_reduce(hipStream_t st, const BatchDesc& bd, const float* rec, const int32_t* vis_tris, float eps,
+                         int mode, double* out, const Readback& rb);
+hipError_t launch_read_back(hipStream_t st, const Readback& rb);
 
 // Gaussian weights over offsets -radius..radius (summing to 1).
 struct GaussW {

@@ -1069,6 +1069,7 @@ struct ItemInfo {
     int pose_local;
     int tile;
     int64_t rec;
+    int slice, slices, slot;   // share of the record's triangles; first slice's slot of a split one
 };
 
 __device__ __forceinline__ bool decode_item(const BatchDesc& bd, ItemInfo& it) {
@@ -1085,6 +1086,9 @@ __device__ __forceinline__ bool decode_item(const BatchDesc& bd, ItemInfo& it) {
     const ScanDesc& sd = bd.s[s];
     const int64_t local = item - sd.item_off;
     it.scan = s;
+    it.slice = 0;
+    it.slices = 1;
+    it.slot = 0;
     it.tile = (int)(local / sd.n_poses);
     it.pose_local = (int)(local % sd.n_poses);
     it.pose = sd.pose_off + it.pose_local;
@@ -1140,13 +1144,17 @@ __device__ __forceinline__ void wave_sums(const T (&v)[N], T (&out)[K]) {
             swap_add16(swap_add32(at(4 * k), at(4 * k + 1)), swap_add32(at(4 * k + 2), at(4 * k + 3)))))));
 }
 
+// Variants of the rasterizer: bins only, with overflow regions, also with
+// records split into slices; and the pass that merges the slices.
+enum Variant { kVarPlain = 0, kVarOverflow = 1, kVarSplit = 2, kVarMerge = 3 };
+
 // Keys of a tile in LDS: rows of TW + 1, so that the rows of one column lie in
 // different banks.
 template <int TW, int TH>
 constexpr int kKeys = (TW + 1) * TH;
 
 // One (scan, pose, tile) item: rasterization, resolve, tile record.
-template <int TW, int TH, int MODE, bool OVF>
+template <int TW, int TH, int MODE, int VAR>
 __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs& a, const ItemInfo& it,
                                           uint64_t* keys, Queues& q, float (*red)[kRecFields]) {
     const ScanDesc& sd = bd.s[it.scan];
@@ -1161,7 +1169,8 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
     tl.x1 = min(tl.x0 + TW, cam.W) - 1; tl.y1 = min(tl.y0 + TH, cam.H) - 1;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
-    for (int p = tid; p < kKeys<TW, TH>; p += kWG) keys[p] = kEmptyKey;
+    if (VAR != kVarMerge)
+        for (int p = tid; p < kKeys<TW, TH>; p += kWG) keys[p] = kEmptyKey;
 
     PoseF P;
     load_pose(a.T_wc + 12 * (int64_t)it.pose, P);
@@ -1169,8 +1178,26 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) P.R[i][j] = uniform(P.R[i][j]);
+    if constexpr (VAR == kVarMerge) {
+        // the nearest of the slices' keys
+        // (16 bytes a load, eight slices in flight)
+        const ulonglong2* slot = reinterpret_cast<const ulonglong2*>(a.split_keys + (int64_t)it.slot * (TW * TH));
+        for (int p = tid; p < TW * TH / 2; p += kWG) {
+            ulonglong2 k = make_ulonglong2(0, 0);
+#pragma unroll 8
+            for (int s = 0; s < it.slices; ++s) {
+                const ulonglong2 x = slot[(int64_t)s * (TW * TH / 2) + p];
+                k.x = max(k.x, x.x);
+                k.y = max(k.y, x.y);
+            }
+            uint64_t* o = keys + (2 * p / TW) * (TW + 1) + 2 * p % TW;
+            o[0] = k.x;
+            o[1] = k.y;
+        }
+        __syncthreads();
+    } else {
     const int ns = a.bin_small[it.rec], nb = a.bin_big[it.rec];
-    if (tid < 2) atomicMax(a.bin_max + tid, tid ? nb : ns);    // one instruction, two lanes
+    if (!a.order && tid < 2) atomicMax(a.bin_max + tid, tid ? nb : ns);    // (an order brings them along)
 
     // Rounds of kWG triangles: from the (pose, tile) bin, large footprints
     // (held at its back) before small ones (at its front), so that near
@@ -1178,11 +1205,12 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
     // its capacity is read from its overflow region, which holds all its
     // entries in the same layout; without one, the tile takes every triangle
     // of every visible cluster of the pose (slower, same result).
-    // (OVF: the call has overflow regions; the kernel without them is
-    // compiled apart, as the mere presence of the region lookup costs the
-    // common case about half a percent)
+    // (the kernel without overflow regions and slices is compiled apart, as
+    // the mere presence of the region lookup costs the common case about half
+    // a percent, that of slices 2 %)
+    constexpr bool OVF = VAR != kVarPlain;
     const bool fits = ns <= a.bin_cap - a.bin_big_cap && nb <= a.bin_big_cap;
-    const int64_t poff = OVF && !fits ? a.pool_off[it.rec] : -1;
+    const int64_t poff = OVF && !fits && a.pool ? a.pool_off[it.rec] : -1;
     const bool use_bin = fits || poff >= 0;
     const int nvis = a.vis_count[it.pose];
     const uint2* vis = a.vis + (int64_t)it.pose * a.n_clusters;
@@ -1203,12 +1231,14 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
     // rasterized, from indices loaded during r - 2 and a bin entry read in r - 3
     TriIn cur;
     uint32_t I1[3];
-    int32_t t1 = entry(0), t2;
+    // a slice takes every dr-th round
+    const int r0 = VAR == kVarSplit ? it.slice : 0, dr = VAR == kVarSplit ? it.slices : 1;
+    int32_t t1 = entry(r0), t2;
     load_indices(a.tri, a.vmax, t1, I1);
     load_vertices(a.xyz, t1, I1, cur);
-    t1 = entry(1);
+    t1 = entry(r0 + dr);
     load_indices(a.tri, a.vmax, t1, I1);
-    t2 = entry(2);
+    t2 = entry(r0 + 2 * dr);
     // Each wave refreshes its quarter of the snapshot after each of its first
     // kSnapEvery chunks and then after every kSnapEvery-th: the near surfaces
     // arrive first, and an older snapshot stays a valid bound (keys only move
@@ -1216,14 +1246,14 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
     if (tid < kSnapTile + kWaves) q.rowmin[tid] = 0.0f;
     WaveQueue& wq = q.w[wave];
     __syncthreads();                           // keys and snapshot are initialized
-    for (int r = 0; r < nr; ++r) {
+    for (int r = r0, n = 0; r < nr; r += dr, ++n) {
         bool two = false;
         int nj = cur.t >= 0 ? setup_triangle<MODE, TW>(keys, wq, lane, q.rowmin, tl, cam, difx, dify, P, cur, 0, &two) : 0;
         const int32_t tc = cur.t;
         load_vertices(a.xyz, t1, I1, cur);
         t1 = t2;
         load_indices(a.tri, a.vmax, t1, I1);
-        t2 = entry(r + 3);
+        t2 = entry(r + 3 * dr);
         raster_jobs<TW>(keys, wq, tl, q.rowmin, lane, nj, dcy);
         // second sub-triangles of triangles clipped at the near plane (rare):
         // their inputs are gathered again, so that they need not stay live
@@ -1241,7 +1271,7 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
         // segment and quarter minimums (w >= 0, so its bits order like its
         // value): the kG lanes of a group cover one kSeg-pixel segment (or,
         // for 8-pixel tile rows, one row)
-        if (r + 1 < nr && (r < kSnapEvery || r % kSnapEvery == 0)) {
+        if (r + dr < nr && (n < kSnapEvery || n % kSnapEvery == 0)) {
             constexpr int kG = TW < kSeg ? TW : kSeg;
             constexpr int kPer = TW * TH / kWaves;         // pixels of a wave's quarter
             uint32_t tmin = 0x7f800000u;
@@ -1259,6 +1289,12 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
         }
     }
     __syncthreads();                           // every wave's keys are in
+    if (VAR == kVarSplit && it.slices > 1) {   // k_merge takes it from here
+        uint64_t* slot = a.split_keys + (int64_t)(it.slot + it.slice) * (TW * TH);
+        for (int p = tid; p < TW * TH; p += kWG) slot[p] = keys[(p / TW) * (TW + 1) + p % TW];
+        return;
+    }
+    }
 
     // ---------------------------------------------------------------- resolve
     Acc acc;
@@ -1460,10 +1496,10 @@ __device__ __forceinline__ void tile_pass(const BatchDesc& bd, const RasterArgs&
 }
 
 // Either one workgroup per item in the XCD-aware order, or, with an item
-// order, persistent workgroups that take the next item of the order (longest
-// first) from a global counter until it runs past the end; every workgroup
-// reaches that exit.
-template <int TW, int TH, int MODE, bool OVF>
+// order, persistent workgroups that take the next item (first the slices of
+// split records, then the order, longest first) from a global counter until
+// it runs past the end; every workgroup reaches that exit.
+template <int TW, int TH, int MODE, int VAR>
 __global__ void __launch_bounds__(kWG, 4) k_raster(BatchDesc bd, RasterArgs a) {
     __shared__ uint64_t keys[kKeys<TW, TH>];
     __shared__ Queues q;
@@ -1471,19 +1507,61 @@ __global__ void __launch_bounds__(kWG, 4) k_raster(BatchDesc bd, RasterArgs a) {
     if (!a.order) {
         ItemInfo it;
         if (!decode_item(bd, it)) return;
-        tile_pass<TW, TH, MODE, OVF>(bd, a, it, keys, q, red);
+        tile_pass<TW, TH, MODE, VAR>(bd, a, it, keys, q, red);
         return;
     }
     __shared__ int slot;
-    for (;;) {
-        __syncthreads();                       // the previous item's shared data is no longer read
-        if (threadIdx.x == 0) slot = atomicAdd(a.queue, 1);
-        __syncthreads();
-        const int k = uniform(slot);
-        if (k >= a.n_order) return;
+    const int n_split = VAR == kVarSplit ? min(a.queue[1], a.split_cap) : 0;
+    const int n = n_split + a.n_order;
+    // (the first item without the counter: a thousand workgroups asking one
+    // address at once, and again to find it past the end, took 0.1 ms)
+    for (int k = blockIdx.x; k < n;) {
         ItemInfo it;
-        decode_rec(bd, a.order[k], it);
-        tile_pass<TW, TH, MODE, OVF>(bd, a, it, keys, q, red);
+        it.slice = 0;
+        it.slices = 1;
+        it.slot = 0;
+        int rec;
+        if (VAR == kVarSplit && k < n_split) {
+            const uint4 e = a.split[k];
+            rec = (int)e.x;
+            it.slice = (int)e.y;
+            it.slices = (int)e.z;
+            it.slot = (int)e.w;
+        } else {
+            rec = a.order[k - n_split];
+        }
+        if (VAR != kVarSplit || rec >= 0) {
+            decode_rec(bd, rec, it);
+            tile_pass<TW, TH, MODE, VAR>(bd, a, it, keys, q, red);
+        }
+        if (n <= (int)gridDim.x) return;
+        __syncthreads();                       // the item's shared data is no longer read
+        if (threadIdx.x == 0) slot = (int)gridDim.x + atomicAdd(a.queue, 1);
+        __syncthreads();
+        k = uniform(slot);
+    }
+}
+
+// The records of split tiles: one workgroup per first slice merges the keys
+// of its record's slices and resolves the tile.  (A launch of its own: the
+// last slice to finish would have to wait for the others' keys to reach
+// memory across the XCDs' caches, a write-back per slice.)
+template <int TW, int TH, int MODE>
+__global__ void __launch_bounds__(kWG, 4) k_merge(BatchDesc bd, RasterArgs a) {
+    __shared__ uint64_t keys[kKeys<TW, TH>];
+    __shared__ Queues q;
+    __shared__ float red[kWG / 64][kRecFields];
+    const int n = min(a.queue[1], a.split_cap);
+    for (int k = blockIdx.x; k < n; k += gridDim.x) {
+        const uint4 e = a.split[k];
+        if ((int)e.x < 0 || e.y != 0) continue;
+        ItemInfo it;
+        it.slice = 0;
+        it.slices = (int)e.z;
+        it.slot = (int)e.w;
+        decode_rec(bd, (int)e.x, it);
+        __syncthreads();                       // the previous record's shared data is no longer read
+        tile_pass<TW, TH, MODE, kVarMerge>(bd, a, it, keys, q, red);
     }
 }
 
@@ -1655,6 +1733,21 @@ __global__ void __launch_bounds__(kVisSortWG) k_vis_sort(BatchDesc bd, int32_t n
 
 // ------------------------------------------------------------------ per-pose reduction
 
+// The call's largest fills and overflow demands to pinned host memory, for the
+// sizing of later calls.
+__device__ __forceinline__ void read_back(const Readback& rb) {
+    if (!rb.host) return;
+    rb.host[1] = rb.bin_max[0];
+    rb.host[4] = rb.bin_max[1];
+    if (rb.spill_top) {
+        *reinterpret_cast<volatile int64_t*>(rb.host + 6) = (int64_t)rb.spill_top[0];
+        *reinterpret_cast<volatile int64_t*>(rb.host + 12) = (int64_t)rb.spill_top[4];
+    }
+}
+__global__ void k_read_back(Readback rb) {
+    if (threadIdx.x == 0) read_back(rb);
+}
+
 // One workgroup per pose: 8 lanes per field sum interleaved tiles (FP64,
 // integers exactly), then the 8 partial sums are added in lane order, so the
 // result does not depend on scheduling.
@@ -1662,7 +1755,8 @@ constexpr int kRedSplit = 8;
 
 __global__ void __launch_bounds__(kRecFields * kRedSplit) k_reduce(BatchDesc bd, const float* __restrict__ rec,
                                                                    const int32_t* __restrict__ vis_tris, float eps,
-                                                                   int mode, double* __restrict__ out) {
+                                                                   int mode, double* __restrict__ out, Readback rb) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) read_back(rb);
     __shared__ double part[kRedSplit][kRecFields];
     __shared__ double val[kRecFields];
     const int pose = blockIdx.x;
@@ -1723,7 +1817,12 @@ __global__ void __launch_bounds__(kRecFields * kRedSplit) k_reduce(BatchDesc bd,
 
 template <int TW, int TH, bool SPILL>
 hipError_t launch_bin_t(hipStream_t st, const BatchDesc& bd, const RasterArgs& a) {
-    const dim3 grid((unsigned)std::min(a.n_clusters > 0 ? a.n_clusters : 1, 256), (unsigned)bd.n_poses);
+    // (256 workgroups a pose keep its bins close to the near-to-far cluster
+    // order; fewer than eight poses take more, 2,048 in all, as they would
+    // leave the device idle: one pose against 1 M triangles bins in 40 us with
+    // 2,048 workgroups, 89 us with 256)
+    const int wide = std::max(256, 2048 / std::max(1, bd.n_poses));
+    const dim3 grid((unsigned)std::min(a.n_clusters > 0 ? a.n_clusters : 1, wide), (unsigned)bd.n_poses);
     int32_t n = 1;
     for (int s = 0; s < bd.n_scans; ++s) n = std::max(n, bd.s[s].tiles_x * bd.s[s].tiles_y);
     n = std::min(n, kBinTable);
@@ -1745,52 +1844,171 @@ hipError_t launch_bin_shape(hipStream_t st, const BatchDesc& bd, const RasterArg
 
 constexpr int kOrderBuckets = 32;
 
+// Share of a workgroup: the call's entries over its resident workgroups.  A
+// record with more entries than that (and kMinSlice) is cut into slices of
+// about that many, so that few or uneven tiles still fill the device: one pose
+// of 640x480 is 150 records whose fullest one used to set the time (350 us of
+// rasterizing; 164 and 24 us of merging in slices).  A slice starts with an
+// empty z-buffer and culls less than the whole record would (1.4 times the
+// instructions there), so records below the share stay whole; slices of half
+// the share made 32 ICP pairs slower (329 against 287 us a call) and one pose
+// no faster.  Calls of more than kSplitRecords records have enough of them.
+constexpr int kMinSlice = 2 * kWG;
+
+// hist: [0, 32) bucket counts, [32, 64) cursors; a.queue[0] while the order is
+// made: entries of the call in units of 64
+__device__ __forceinline__ uint32_t slice_size(uint32_t total64, int resident) {
+    return (uint32_t)max((int64_t)kMinSlice, (int64_t)total64 * 64 / resident);
+}
+
 // bucket 0 holds the costliest records: 31 - floor(log2(fill + 1))
-__device__ __forceinline__ int order_bucket(const int32_t* bs, const int32_t* bb, int64_t r) {
-    const uint32_t c = (uint32_t)bs[r] + (uint32_t)bb[r] + 1u;
-    return __clz(c);
+__device__ __forceinline__ int order_bucket(uint32_t fill) { return __clz((int)(fill + 1u)); }
+
+// Record at position `item` of the item order (per scan tile-major, poses of a
+// tile adjacent), so that each workgroup's run of a bucket keeps neighbouring
+// poses of the same tiles, which read the same triangles, together.
+__device__ __forceinline__ int64_t item_record(const BatchDesc& bd, int64_t item) {
+    int sc = 0;
+    while (sc + 1 < bd.n_scans && item >= bd.s[sc + 1].item_off) ++sc;
+    const ScanDesc& sd = bd.s[sc];
+    const int64_t local = item - sd.item_off;
+    return sd.rec_off + (local % sd.n_poses) * (int64_t)(sd.tiles_x * sd.tiles_y) + local / sd.n_poses;
+}
+
+// Cuts a record into slices if it has too many entries and slots are left;
+// true if it was cut.  cursor: taken slots.
+__device__ __forceinline__ bool split_record(uint4* split, int cap, int* cursor, int64_t r, uint32_t fill, uint32_t size) {
+    if (fill <= size || cap == 0) return false;
+    const int n = (int)min((fill + size - 1) / size, (uint32_t)kMaxSlices);
+    const int pos = atomicAdd(cursor, n);
+    const bool fits = pos + n <= cap;
+    for (int k = 0; k < n && pos + k < cap; ++k)
+        split[pos + k] = make_uint4(fits ? (uint32_t)r : 0xffffffffu, (uint32_t)k, (uint32_t)n, (uint32_t)pos);
+    return fits;
+}
+
+// The whole order in one workgroup, for calls of up to kOrderOne records (7 to
+// 12 us; three launches took 14): the lanes of a wave that share a bucket take
+// their places with one atomic.
+constexpr int kOrderWG = 1024;
+constexpr int64_t kOrderOne = 16384;
+
+__device__ __forceinline__ int bucket_place(int* counter, int b, bool live) {
+    const int lane = threadIdx.x & 63;
+    uint64_t todo = __ballot(live);
+    int pos = 0;
+    while (todo) {
+        const int first = __ffsll((unsigned long long)todo) - 1;
+        const int bb = __builtin_amdgcn_readlane(b, first);
+        const uint64_t m = __ballot(live && b == bb) & todo;
+        int base = 0;
+        if (lane == first) base = atomicAdd(counter + bb, __popcll(m));
+        base = __builtin_amdgcn_readlane(base, first);
+        if ((m >> lane) & 1) pos = base + __popcll(m & ((1ull << lane) - 1ull));
+        todo &= ~m;
+    }
+    return pos;
+}
+
+__global__ void __launch_bounds__(kOrderWG) k_order_one(BatchDesc bd, const int32_t* __restrict__ bs,
+                                                        const int32_t* __restrict__ bb, int n, int resident,
+                                                        uint4* __restrict__ split, int split_cap,
+                                                        int32_t* __restrict__ queue, int32_t* __restrict__ order,
+                                                        int32_t* __restrict__ bin_max) {
+    __shared__ int cnt[kOrderBuckets], cur[kOrderBuckets], slots;
+    __shared__ uint32_t total;
+    const int tid = threadIdx.x;
+    if (tid < kOrderBuckets) cnt[tid] = 0;
+    if (tid == 0) { slots = 0; total = 0; }
+    __syncthreads();
+    uint32_t sum = 0;
+    int ms = 0, mb = 0;
+    for (int i0 = 0; i0 < n; i0 += kOrderWG) {
+        const int r = i0 + tid;
+        const bool live = r < n;
+        const int fs = live ? bs[r] : 0, fb = live ? bb[r] : 0;
+        const uint32_t fill = (uint32_t)fs + (uint32_t)fb;
+        ms = max(ms, fs);
+        mb = max(mb, fb);
+        sum += (fill + 63) >> 6;
+        bucket_place(cnt, order_bucket(fill), live);
+    }
+    sum = (uint32_t)wave_scan_add((int)sum);
+    ms = wave_scan_max(ms);
+    mb = wave_scan_max(mb);
+    if ((tid & 63) == 63) {
+        atomicAdd(&total, sum);
+        atomicMax(bin_max, ms);
+        atomicMax(bin_max + 1, mb);
+    }
+    __syncthreads();
+    if (tid < 64) {
+        const int c = tid < kOrderBuckets ? cnt[tid] : 0;
+        const int inc = wave_scan_add(c);
+        if (tid < kOrderBuckets) cur[tid] = inc - c;
+    }
+    __syncthreads();
+    const uint32_t size = slice_size(total, resident);
+    for (int i0 = 0; i0 < n; i0 += kOrderWG) {
+        const int item = i0 + tid;
+        const bool live = item < n;
+        const int64_t r = live ? item_record(bd, item) : 0;
+        const uint32_t fill = live ? (uint32_t)bs[r] + (uint32_t)bb[r] : 0u;
+        const int pos = bucket_place(cur, order_bucket(fill), live);
+        if (live) order[pos] = split_record(split, split_cap, &slots, r, fill, size) ? -1 : (int32_t)r;
+    }
+    __syncthreads();
+    if (tid == 0) queue[1] = slots;
 }
 
 __global__ void __launch_bounds__(kWG) k_order_count(const int32_t* __restrict__ bs, const int32_t* __restrict__ bb,
-                                                     int64_t n, int32_t* __restrict__ hist) {
-    __shared__ int h[kOrderBuckets];
+                                                     int64_t n, int32_t* __restrict__ hist, int32_t* __restrict__ queue,
+                                                     int32_t* __restrict__ bin_max) {
+    __shared__ int h[kOrderBuckets], sum, top[2];
     if (threadIdx.x < kOrderBuckets) h[threadIdx.x] = 0;
+    if (threadIdx.x == 0) { sum = 0; top[0] = 0; top[1] = 0; }
     __syncthreads();
     const int64_t r = (int64_t)blockIdx.x * kWG + threadIdx.x;
-    if (r < n) atomicAdd(&h[order_bucket(bs, bb, r)], 1);
+    const int fs = r < n ? bs[r] : 0, fb = r < n ? bb[r] : 0;
+    const uint32_t fill = (uint32_t)fs + (uint32_t)fb;
+    if (r < n) atomicAdd(&h[order_bucket(fill)], 1);
+    const int ws = wave_scan_add((int)((fill + 63) >> 6)), ms = wave_scan_max(fs), mb = wave_scan_max(fb);
+    if ((threadIdx.x & 63) == 63) {
+        atomicAdd(&sum, ws);
+        atomicMax(&top[0], ms);
+        atomicMax(&top[1], mb);
+    }
     __syncthreads();
+    if (threadIdx.x == 0 && sum) atomicAdd(queue, sum);
+    if (threadIdx.x < 2 && top[threadIdx.x]) atomicMax(bin_max + threadIdx.x, top[threadIdx.x]);
     if (threadIdx.x < kOrderBuckets && h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
 }
 
-// hist[0..31] counts -> hist[32..63] running cursors (exclusive prefix)
-__global__ void k_order_offsets(int32_t* hist) {
+// hist[0..31] counts -> hist[32..63] running cursors (exclusive prefix); the
+// slice size in their place, and the queue starts from zero
+__global__ void k_order_offsets(int32_t* hist, int32_t* queue, int resident) {
     if (threadIdx.x != 0) return;
     int acc = 0;
     for (int k = 0; k < kOrderBuckets; ++k) {
         hist[kOrderBuckets + k] = acc;
         acc += hist[k];
     }
+    hist[0] = (int32_t)slice_size((uint32_t)queue[0], resident);
+    queue[0] = 0;
 }
 
-// Records are visited in item order (per scan tile-major, poses of a tile
-// adjacent), so that each workgroup's run of a bucket keeps neighbouring poses
-// of the same tiles, which read the same triangles, together.
 __global__ void __launch_bounds__(kWG) k_order_scatter(BatchDesc bd, const int32_t* __restrict__ bs,
                                                        const int32_t* __restrict__ bb, int64_t n,
-                                                       int32_t* __restrict__ hist, int32_t* __restrict__ order) {
+                                                       int32_t* __restrict__ hist, uint4* __restrict__ split,
+                                                       int split_cap, int32_t* __restrict__ queue,
+                                                       int32_t* __restrict__ order) {
     __shared__ int h[kOrderBuckets], base[kOrderBuckets];
     if (threadIdx.x < kOrderBuckets) h[threadIdx.x] = 0;
     __syncthreads();
     const int64_t item = (int64_t)blockIdx.x * kWG + threadIdx.x;
-    int64_t r = n;
-    if (item < n) {
-        int sc = 0;
-        while (sc + 1 < bd.n_scans && item >= bd.s[sc + 1].item_off) ++sc;
-        const ScanDesc& sd = bd.s[sc];
-        const int64_t local = item - sd.item_off;
-        r = sd.rec_off + (local % sd.n_poses) * (int64_t)(sd.tiles_x * sd.tiles_y) + local / sd.n_poses;
-    }
-    const int b = r < n ? order_bucket(bs, bb, r) : 0;
+    const int64_t r = item < n ? item_record(bd, item) : n;
+    const uint32_t fill = r < n ? (uint32_t)bs[r] + (uint32_t)bb[r] : 0u;
+    const int b = order_bucket(fill);
     if (r < n) atomicAdd(&h[b], 1);
     __syncthreads();
     if (threadIdx.x < kOrderBuckets) {
@@ -1799,24 +2017,35 @@ __global__ void __launch_bounds__(kWG) k_order_scatter(BatchDesc bd, const int32
         h[threadIdx.x] = 0;
     }
     __syncthreads();
-    if (r < n) order[base[b] + atomicAdd(&h[b], 1)] = (int32_t)r;
+    if (r < n)
+        order[base[b] + atomicAdd(&h[b], 1)] =
+            split_record(split, split_cap, queue + 1, r, fill, (uint32_t)hist[0]) ? -1 : (int32_t)r;
+}
+
+template <int TW, int TH, int VAR>
+void launch_raster_v(hipStream_t st, dim3 grid, const BatchDesc& bd, const RasterArgs& a, int mode) {
+    if (mode == kRender) hipLaunchKernelGGL((k_raster<TW, TH, kRender, VAR>), grid, dim3(kWG), 0, st, bd, a);
+    else if (mode == kCost) hipLaunchKernelGGL((k_raster<TW, TH, kCost, VAR>), grid, dim3(kWG), 0, st, bd, a);
+    else if (mode == kIcp) hipLaunchKernelGGL((k_raster<TW, TH, kIcp, VAR>), grid, dim3(kWG), 0, st, bd, a);
+    else hipLaunchKernelGGL((k_raster<TW, TH, kGrad, VAR>), grid, dim3(kWG), 0, st, bd, a);
 }
 
 template <int TW, int TH>
 hipError_t launch_raster_t(hipStream_t st, const BatchDesc& bd, const RasterArgs& a, int mode) {
     const int64_t chunk = (bd.n_items + 7) / 8;
-    const dim3 grid(a.order ? (unsigned)std::min<int64_t>(persistent_grid(TW, TH, mode), a.n_order)
+    const dim3 grid(a.order ? (unsigned)std::min<int64_t>(persistent_grid(TW, TH, mode), (int64_t)a.n_order + a.split_cap)
                             : (unsigned)(chunk * 8));
-    if (a.spill) {
-        if (mode == kRender) hipLaunchKernelGGL((k_raster<TW, TH, kRender, true>), grid, dim3(kWG), 0, st, bd, a);
-        else if (mode == kCost) hipLaunchKernelGGL((k_raster<TW, TH, kCost, true>), grid, dim3(kWG), 0, st, bd, a);
-        else if (mode == kIcp) hipLaunchKernelGGL((k_raster<TW, TH, kIcp, true>), grid, dim3(kWG), 0, st, bd, a);
-        else hipLaunchKernelGGL((k_raster<TW, TH, kGrad, true>), grid, dim3(kWG), 0, st, bd, a);
+    if (a.split_cap > 0) {
+        launch_raster_v<TW, TH, kVarSplit>(st, grid, bd, a, mode);
+        const dim3 mg((unsigned)std::min(a.split_cap, 2048));
+        if (mode == kRender) hipLaunchKernelGGL((k_merge<TW, TH, kRender>), mg, dim3(kWG), 0, st, bd, a);
+        else if (mode == kCost) hipLaunchKernelGGL((k_merge<TW, TH, kCost>), mg, dim3(kWG), 0, st, bd, a);
+        else if (mode == kIcp) hipLaunchKernelGGL((k_merge<TW, TH, kIcp>), mg, dim3(kWG), 0, st, bd, a);
+        else hipLaunchKernelGGL((k_merge<TW, TH, kGrad>), mg, dim3(kWG), 0, st, bd, a);
+    } else if (a.spill) {
+        launch_raster_v<TW, TH, kVarOverflow>(st, grid, bd, a, mode);
     } else {
-        if (mode == kRender) hipLaunchKernelGGL((k_raster<TW, TH, kRender, false>), grid, dim3(kWG), 0, st, bd, a);
-        else if (mode == kCost) hipLaunchKernelGGL((k_raster<TW, TH, kCost, false>), grid, dim3(kWG), 0, st, bd, a);
-        else if (mode == kIcp) hipLaunchKernelGGL((k_raster<TW, TH, kIcp, false>), grid, dim3(kWG), 0, st, bd, a);
-        else hipLaunchKernelGGL((k_raster<TW, TH, kGrad, false>), grid, dim3(kWG), 0, st, bd, a);
+        launch_raster_v<TW, TH, kVarPlain>(st, grid, bd, a, mode);
     }
     return hipGetLastError();
 }
@@ -1858,13 +2087,21 @@ hipError_t launch_overflow(hipStream_t st, const RasterArgs& a, int64_t n_record
     return hipGetLastError();
 }
 
-hipError_t launch_order(hipStream_t st, const BatchDesc& bd, const int32_t* bin_small, const int32_t* bin_big,
-                        int64_t n_records, int32_t* hist, int32_t* order) {
+hipError_t launch_order(hipStream_t st, const BatchDesc& bd, const RasterArgs& a, int64_t n_records, int32_t* hist,
+                        int32_t* order, uint4* split, int mode) {
     if (n_records <= 0) return hipSuccess;
+    const int resident = persistent_grid(bd.tile_w, bd.tile_h, mode);
+    if (n_records <= kOrderOne) {
+        hipLaunchKernelGGL(k_order_one, dim3(1), dim3(kOrderWG), 0, st, bd, a.bin_small, a.bin_big, (int)n_records,
+                           resident, split, a.split_cap, a.queue, order, a.bin_max);
+        return hipGetLastError();
+    }
     const unsigned g = (unsigned)((n_records + kWG - 1) / kWG);
-    hipLaunchKernelGGL(k_order_count, dim3(g), dim3(kWG), 0, st, bin_small, bin_big, n_records, hist);
-    hipLaunchKernelGGL(k_order_offsets, dim3(1), dim3(64), 0, st, hist);
-    hipLaunchKernelGGL(k_order_scatter, dim3(g), dim3(kWG), 0, st, bd, bin_small, bin_big, n_records, hist, order);
+    hipLaunchKernelGGL(k_order_count, dim3(g), dim3(kWG), 0, st, a.bin_small, a.bin_big, n_records, hist, a.queue,
+                       a.bin_max);
+    hipLaunchKernelGGL(k_order_offsets, dim3(1), dim3(64), 0, st, hist, a.queue, resident);
+    hipLaunchKernelGGL(k_order_scatter, dim3(g), dim3(kWG), 0, st, bd, a.bin_small, a.bin_big, n_records, hist, split,
+                       a.split_cap, a.queue, order);
     return hipGetLastError();
 }
 
@@ -1874,7 +2111,7 @@ int resident_blocks() {
     static int cached = 0;
     if (!cached) {
         int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_raster<TW, TH, MODE, false>, kWG, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_raster<TW, TH, MODE, kVarPlain>, kWG, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
             (void)hipGetLastError();
@@ -1909,10 +2146,15 @@ hipError_t launch_raster(hipStream_t st, const BatchDesc& bd, const RasterArgs& 
 }
 
 hipError_t launch_reduce(hipStream_t st, const BatchDesc& bd, const float* rec, const int32_t* vis_tris,
-                         float eps, int mode, double* out) {
+                         float eps, int mode, double* out, const Readback& rb) {
     if (bd.n_poses == 0) return hipSuccess;
     hipLaunchKernelGGL(k_reduce, dim3((unsigned)bd.n_poses), dim3(kRecFields * kRedSplit), 0, st, bd, rec, vis_tris,
-                       eps, mode, out);
+                       eps, mode, out, rb);
+    return hipGetLastError();
+}
+
+hipError_t launch_read_back(hipStream_t st, const Readback& rb) {
+    hipLaunchKernelGGL(k_read_back, dim3(1), dim3(64), 0, st, rb);
     return hipGetLastError();
 }
 
