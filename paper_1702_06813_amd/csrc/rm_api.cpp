@@ -931,17 +931,12 @@ int rm_mesh_from_range(rm_ctx* ctx, const float* depth, rm_camera cam, const dou
     const int64_t nn = (int64_t)gh * gw;
     const int64_t nb = meshify_blocks(cam.height, cam.width, stride);
     Carve cv;
-    const size_t o_kind = cv.take<uint8_t>(nn);
-    const size_t o_cnt = cv.take<int32_t>(nb);
+    const size_t o_mask = cv.take<uint64_t>(2 * nb);
     const size_t o_off = cv.take<int32_t>(nb);
-    const size_t o_tot = cv.take<int32_t>(1);
     rc = ensure_scratch(ctx, cv.off);
     if (rc) return rc;
     RM_HIP(ctx, launch_meshify(ctx->stream, depth, cam, T_wc, stride, smooth_radius, z_min, z_max, max_edge, xyz_out, tri_out,
-                               cls_out, cap_t, at<uint8_t>(ctx, o_kind), at<int32_t>(ctx, o_cnt),
-                               at<int32_t>(ctx, o_off), at<int32_t>(ctx, o_tot)));
-    RM_HIP(ctx, hipMemcpyAsync(ctx->pinned, at<int32_t>(ctx, o_tot), sizeof(int32_t), hipMemcpyDeviceToHost,
-                               ctx->stream));
+                               cls_out, cap_t, at<uint64_t>(ctx, o_mask), at<int32_t>(ctx, o_off), ctx->pinned));
     RM_HIP(ctx, hipStreamSynchronize(ctx->stream));
     *n_v_out = nn;
     *n_t_out = ctx->pinned[0];

@@ -31,98 +31,150 @@ struct Pose12 { double m[12]; };
 
 // Grid node (i, j) sits at pixel (j*s, i*s).  A valid node's depth is the
 // FP64 mean of the valid pixels of the (2R+1)^2 window around it whose depth
-// is within RM_SMOOTH_REL of the node pixel's (R = 0: the node pixel).
-// Back-projection in FP64 at that depth (z_max for a no-return), world
-// transform in FP64, one rounding to f32 at the end.  Dead nodes get NaN.
-__global__ void k_mesh_nodes(const float* __restrict__ depth, int32_t H, int32_t W, int32_t s, int32_t R,
-                             int32_t gh, int32_t gw, float fx, float fy, float cx, float cy,
-                             Pose12 T, float z_min, float z_max, float* __restrict__ xyz,
-                             uint8_t* __restrict__ kind) {
-    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= (int64_t)gh * gw) return;
-    const int i = (int)(n / gw), j = (int)(n % gw);
-    const int py = i * s, px = j * s;
-    const float z = depth[(int64_t)py * W + px];
-    const int k = range_class(z, z_min, z_max);
-    kind[n] = (uint8_t)k;
-    if (k == kDead) {
-        const float q = __int_as_float(0x7fc00000);
-        xyz[3 * n] = q; xyz[3 * n + 1] = q; xyz[3 * n + 2] = q;
-        return;
-    }
-    double zd = (k == kNoReturn) ? (double)z_max : (double)z;
-    if (k == kValid && R > 0) {
+// is within RM_SMOOTH_REL of the node pixel's (R = 0: the node pixel); the
+// kept depths differ by 3 % at most, so their FP64 sum (at most 1,089 of them)
+// is exact and its order free.  Back-projection in FP64 at that depth (z_max
+// for a no-return), world transform in FP64, one rounding to f32 at the end.
+// Dead nodes get NaN.  G lanes share a node's window, row by row.
+struct MeshArgs {
+    const float* depth;
+    int32_t H, W, s, R, gh, gw;
+    float fx, fy, cx, cy, z_min, z_max;
+    Pose12 T;
+};
+
+// at(y, x): the depth image's pixel.
+template <int G, typename At>
+__device__ __forceinline__ int mesh_node(const MeshArgs& m, At at, int i, int j, int sub, float out[3]) {
+    const int py = i * m.s, px = j * m.s;
+    const float z = at(py, px);
+    const int k = range_class(z, m.z_min, m.z_max);
+    double zd = (k == kNoReturn) ? (double)m.z_max : (double)z;
+    if (G > 1) {
         const double zc = (double)z, tol = RM_SMOOTH_REL * zc;
         double sum = 0.0;
         int cnt = 0;
-        for (int yy = max(py - R, 0); yy <= min(py + R, H - 1); ++yy)
-            for (int xx = max(px - R, 0); xx <= min(px + R, W - 1); ++xx) {
-                const float zn = depth[(int64_t)yy * W + xx];
-                if (range_class(zn, z_min, z_max) != kValid) continue;
-                if (fabs((double)zn - zc) <= tol) { sum += (double)zn; ++cnt; }
+        if (k == kValid)
+            for (int yy = max(py - m.R, 0) + sub; yy <= min(py + m.R, m.H - 1); yy += G) {
+                const int x1 = min(px + m.R, m.W - 1);
+#pragma unroll 4
+                for (int xx = max(px - m.R, 0); xx <= x1; ++xx) {
+                    const float zn = at(yy, xx);
+                    // (valid, without branches; NaN fails every test)
+                    const bool in = (zn > 0.0f) & (zn >= m.z_min) & (zn <= m.z_max) & (fabs((double)zn - zc) <= tol);
+                    sum += in ? (double)zn : 0.0;
+                    cnt += in;
+                }
             }
-        zd = sum / (double)cnt;
+#pragma unroll
+        for (int off = G / 2; off > 0; off >>= 1) {
+            sum += __shfl_xor(sum, off);
+            cnt += __shfl_xor(cnt, off);
+        }
+        if (k == kValid) zd = sum / (double)cnt;
     }
-    const double xc = zd * (((double)px - (double)cx) / (double)fx);
-    const double yc = zd * (((double)py - (double)cy) / (double)fy);
+    const double xc = zd * (((double)px - (double)m.cx) / (double)m.fx);
+    const double yc = zd * (((double)py - (double)m.cy) / (double)m.fy);
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
-        const double w = ((T.m[4 * r] * xc + T.m[4 * r + 1] * yc) + T.m[4 * r + 2] * zd) + T.m[4 * r + 3];
-        xyz[3 * n + r] = (float)w;
+        const double w = ((m.T.m[4 * r] * xc + m.T.m[4 * r + 1] * yc) + m.T.m[4 * r + 2] * zd) + m.T.m[4 * r + 3];
+        out[r] = k == kDead ? __int_as_float(0x7fc00000) : (float)w;
     }
+    return k;
 }
 
-// Quad (qi, qj) between nodes (qi,qj) (qi,qj+1) (qi+1,qj) (qi+1,qj+1):
-// returns 0 = dropped (a dead corner), 1 = free-occupied, 2 = free-unknown.
-__device__ __forceinline__ int quad_state(const float* __restrict__ xyz, const uint8_t* __restrict__ kind,
-                                          int gw, int qi, int qj, double lim2) {
-    const int64_t n00 = (int64_t)qi * gw + qj;
-    const int64_t c[4] = {n00, n00 + 1, n00 + gw + 1, n00 + gw};   // perimeter order
-    int dead = 0, noret = 0;
+// One workgroup per 8x8 block of quads: the nodes of its 9x9 corners (a corner
+// on a shared side is computed by each block that needs it and written by the
+// one to its lower right), then a wave classifies the quads, lane = row*8 +
+// col.  Quad (qi, qj) between nodes (qi,qj) (qi,qj+1) (qi+1,qj) (qi+1,qj+1)
+// is dropped with a dead corner, free-unknown with a no-return corner or a
+// side beyond the limit, else free-occupied.  masks[2 blk] = quads kept,
+// masks[2 blk + 1] = free-unknown ones.  Latency sets the time: a 160x120 grid
+// with 9x9 windows takes 12 us here; a lane per node and launches of their own
+// for nodes and quads took 25 us, on 75 workgroups, window pixels read from
+// memory instead of LDS 15 us.
+constexpr int kNodeSide = kQuadBlock + 1;
+
+// PATCH: the windows of the block's nodes, patch x patch pixels, are staged in
+// LDS first (dynamic, patch^2 floats).
+constexpr int kMaxPatch = 88;              // 30 KB: stride 8 with R = 11, stride 6 with R = 19
+
+template <int G, bool PATCH>
+__global__ void __launch_bounds__(kWG) k_mesh_block(MeshArgs m, int bw, double lim2, int patch,
+                                                    float* __restrict__ xyz, uint64_t* __restrict__ masks) {
+    extern __shared__ float stage[];
+    __shared__ float v[kNodeSide * kNodeSide][3];
+    __shared__ int kind[kNodeSide * kNodeSide];
+    const int blk = blockIdx.x;
+    const int i0 = blk / bw * kQuadBlock, j0 = blk % bw * kQuadBlock;
+    constexpr int kNodes = kNodeSide * kNodeSide, kPer = kWG / G;
+    const int y0 = max(i0 * m.s - m.R, 0), x0 = max(j0 * m.s - m.R, 0);
+    if (PATCH) {
+        for (int p = threadIdx.x; p < patch * patch; p += kWG) {
+            const int y = y0 + p / patch, x = x0 + p % patch;
+            if (y < m.H && x < m.W) stage[p] = m.depth[(int64_t)y * m.W + x];
+        }
+        __syncthreads();
+    }
+    auto at = [&](int y, int x) {
+        return PATCH ? stage[(y - y0) * patch + x - x0] : m.depth[(int64_t)y * m.W + x];
+    };
+    for (int n0 = 0; n0 < kNodes; n0 += kPer) {
+        const int n = n0 + threadIdx.x / G, sub = threadIdx.x % G;
+        const int a = n / kNodeSide, b = n % kNodeSide, i = i0 + a, j = j0 + b;
+        float p[3];
+        int k = kDead;
+        const bool node = n < kNodes && i < m.gh && j < m.gw;
+        // (whole groups of G lanes share n, so a group takes this branch together)
+        if (node) k = mesh_node<G>(m, at, i, j, sub, p);
+        if (n < kNodes && sub == 0) {
+            kind[n] = k;
+            if (node) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int kk = kind[c[k]];
-        dead |= kk == kDead;
-        noret |= kk == kNoReturn;
-    }
-    if (dead) return 0;
-    int big = 0;
+                for (int r = 0; r < 3; ++r) v[n][r] = p[r];
+                if ((a < kQuadBlock || i == m.gh - 1) && (b < kQuadBlock || j == m.gw - 1)) {
+                    float* o = xyz + 3 * ((int64_t)i * m.gw + j);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float* a = xyz + 3 * c[k];
-        const float* b = xyz + 3 * c[(k + 1) & 3];
-        const double dx = (double)a[0] - (double)b[0];
-        const double dy = (double)a[1] - (double)b[1];
-        const double dz = (double)a[2] - (double)b[2];
-        big |= ((dx * dx + dy * dy) + dz * dz) > lim2;
+                    for (int r = 0; r < 3; ++r) o[r] = p[r];
+                }
+            }
+        }
     }
-    return (noret || big) ? 2 : 1;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int lane = threadIdx.x, a = lane / kQuadBlock, b = lane % kQuadBlock;
+    bool keep = i0 + a < m.gh - 1 && j0 + b < m.gw - 1, fu = false;
+    const int n00 = a * kNodeSide + b;
+    const int c[4] = {n00, n00 + 1, n00 + kNodeSide + 1, n00 + kNodeSide};   // perimeter order
+    if (keep) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int kk = kind[c[k]];
+            keep &= kk != kDead;
+            fu |= kk == kNoReturn;
+            const float* p = v[c[k]];
+            const float* q = v[c[(k + 1) & 3]];
+            const double dx = (double)p[0] - (double)q[0];
+            const double dy = (double)p[1] - (double)q[1];
+            const double dz = (double)p[2] - (double)q[2];
+            fu |= ((dx * dx + dy * dy) + dz * dz) > lim2;
+        }
+    }
+    const uint64_t mk = __ballot(keep), mf = __ballot(keep && fu);
+    if (lane == 0) { masks[2 * (int64_t)blk] = mk; masks[2 * (int64_t)blk + 1] = mf; }
 }
 
-// One wave64 per 8x8 block of quads: lane = row*8 + col inside the block.
-__global__ void k_mesh_count(const float* __restrict__ xyz, const uint8_t* __restrict__ kind, int gh,
-                             int gw, int bw, int64_t n_blocks, double lim2,
-                             int32_t* __restrict__ counts) {
-    const int64_t blk = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x / 64);
-    const int lane = threadIdx.x & 63;
-    if (blk >= n_blocks) return;
-    const int qi = (int)(blk / bw) * kQuadBlock + lane / kQuadBlock;
-    const int qj = (int)(blk % bw) * kQuadBlock + lane % kQuadBlock;
-    int st = 0;
-    if (qi < gh - 1 && qj < gw - 1) st = quad_state(xyz, kind, gw, qi, qj, lim2);
-    const uint64_t m = __ballot(st != 0);
-    if (lane == 0) counts[blk] = 2 * __popcll(m);
-}
+// Exclusive prefix sum of the block counts (one workgroup of 1024 threads),
+// for grids of more than kDirectBlocks blocks.
+constexpr int64_t kDirectBlocks = 4096;
 
-// Exclusive prefix sum of the block counts (one workgroup of 1024 threads).
-__global__ void k_mesh_scan(const int32_t* __restrict__ counts, int64_t n, int32_t* __restrict__ offsets,
-                            int32_t* __restrict__ total) {
+__global__ void k_mesh_scan(const uint64_t* __restrict__ masks, int64_t n, int32_t* __restrict__ offsets) {
     __shared__ int64_t part[1024];
     const int t = threadIdx.x;
     const int64_t per = (n + 1023) / 1024;
     const int64_t b = t * per, e = b + per < n ? b + per : n;
     int64_t s = 0;
-    for (int64_t k = b; k < e; ++k) s += counts[k];
+    for (int64_t k = b; k < e; ++k) s += 2 * __popcll(masks[2 * k]);
     part[t] = s;
     __syncthreads();
     for (int off = 1; off < 1024; off <<= 1) {
@@ -132,32 +184,57 @@ __global__ void k_mesh_scan(const int32_t* __restrict__ counts, int64_t n, int32
         __syncthreads();
     }
     int64_t run = part[t] - s;
-    for (int64_t k = b; k < e; ++k) { offsets[k] = (int32_t)run; run += counts[k]; }
-    if (t == 1023) *total = (int32_t)part[1023];
+    for (int64_t k = b; k < e; ++k) { offsets[k] = (int32_t)run; run += 2 * __popcll(masks[2 * k]); }
 }
 
-__global__ void k_mesh_emit(const float* __restrict__ xyz, const uint8_t* __restrict__ kind, int gh,
-                            int gw, int bw, int64_t n_blocks, double lim2,
-                            const int32_t* __restrict__ offsets, int64_t cap_t,
-                            int32_t* __restrict__ tri, uint8_t* __restrict__ cls) {
-    const int64_t blk = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x / 64);
-    const int lane = threadIdx.x & 63;
+// Triangles of four blocks per workgroup, a wave each.  Without offsets
+// (grids of up to kDirectBlocks blocks) each workgroup sums the counts before
+// its own blocks, which is cheaper than a launch of its own.  The last wave
+// writes the total to pinned host memory.
+__global__ void __launch_bounds__(kWG) k_mesh_emit(const uint64_t* __restrict__ masks, int gw, int bw, int64_t n_blocks,
+                                                   const int32_t* __restrict__ offsets, int64_t cap_t,
+                                                   int32_t* __restrict__ tri, uint8_t* __restrict__ cls,
+                                                   int32_t* __restrict__ total) {
+    __shared__ int part[kWG / 64];
+    const int wave = threadIdx.x / 64, lane = threadIdx.x & 63;
+    const int64_t b0 = (int64_t)blockIdx.x * (kWG / 64), blk = b0 + wave;
+    int64_t base = 0;
+    if (!offsets) {
+        int s = 0;
+        for (int64_t k = threadIdx.x; k < b0; k += kWG) s += 2 * __popcll(masks[2 * k]);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+        if (lane == 0) part[wave] = s;
+        __syncthreads();
+        base = part[0] + part[1] + part[2] + part[3];
+        for (int64_t k = b0; k < min(blk, n_blocks); ++k) base += 2 * __popcll(masks[2 * k]);
+    }
     if (blk >= n_blocks) return;
+    if (offsets) base = offsets[blk];
+    const uint64_t m = masks[2 * blk], mf = masks[2 * blk + 1];
+    if (blk == n_blocks - 1 && lane == 0) *total = (int32_t)(base + 2 * __popcll(m));
+    if (!((m >> lane) & 1)) return;
     const int qi = (int)(blk / bw) * kQuadBlock + lane / kQuadBlock;
     const int qj = (int)(blk % bw) * kQuadBlock + lane % kQuadBlock;
-    int st = 0;
-    if (qi < gh - 1 && qj < gw - 1) st = quad_state(xyz, kind, gw, qi, qj, lim2);
-    const uint64_t m = __ballot(st != 0);
-    if (!st) return;
-    const int before = __popcll(m & ((1ull << lane) - 1ull));
-    const int64_t t0 = (int64_t)offsets[blk] + 2 * before;
+    const int64_t t0 = base + 2 * __popcll(m & ((1ull << lane) - 1ull));
     if (t0 + 2 > cap_t) return;                 // host reports RM_ERR_CAPACITY from the total
     const int32_t n00 = qi * gw + qj, n01 = n00 + 1, n10 = n00 + gw, n11 = n10 + 1;
-    const uint8_t c = st == 2 ? RM_FU : RM_FO;
+    const uint8_t c = (mf >> lane) & 1 ? RM_FU : RM_FO;
     tri[3 * t0] = n00; tri[3 * t0 + 1] = n01; tri[3 * t0 + 2] = n11;
     tri[3 * t0 + 3] = n00; tri[3 * t0 + 4] = n11; tri[3 * t0 + 5] = n10;
     cls[t0] = c;
     cls[t0 + 1] = c;
+}
+
+// A grid without quads (a single row or column of nodes).
+__global__ void k_mesh_nodes(MeshArgs m, float* __restrict__ xyz, int32_t* __restrict__ total) {
+    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (n == 0) *total = 0;
+    if (n / 8 >= (int64_t)m.gh * m.gw) return;
+    float p[3];
+    mesh_node<8>(m, [&](int y, int x) { return m.depth[(int64_t)y * m.W + x]; }, (int)(n / 8 / m.gw), (int)(n / 8 % m.gw), (int)(n % 8), p);
+    if (n % 8 == 0)
+        for (int r = 0; r < 3; ++r) xyz[3 * (n / 8) + r] = p[r];
 }
 
 // Cluster bounds: one workgroup per cluster of kClusterTris triangles.
@@ -238,27 +315,36 @@ hipError_t launch_scan_image(hipStream_t st, const float* depth, int32_t H, int3
 
 hipError_t launch_meshify(hipStream_t st, const float* depth, rm_camera cam, const double* T,
                           int32_t stride, int32_t smooth_radius, float z_min, float z_max, float max_edge,
-                          float* xyz, int32_t* tri, uint8_t* cls, int64_t cap_t, uint8_t* kind,
-                          int32_t* block_counts, int32_t* block_offsets, int32_t* total) {
-    const int32_t H = cam.height, W = cam.width;
-    const int32_t gh = (H + stride - 1) / stride, gw = (W + stride - 1) / stride;
-    Pose12 P;
-    for (int k = 0; k < 12; ++k) P.m[k] = T[k];
-    const int64_t nn = (int64_t)gh * gw;
-    hipLaunchKernelGGL(k_mesh_nodes, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, st, depth, H, W,
-                       stride, smooth_radius, gh, gw, cam.fx, cam.fy, cam.cx, cam.cy, P, z_min, z_max, xyz, kind);
-    const int64_t nb = meshify_blocks(H, W, stride);
-    const int bw = (gw - 1 + kQuadBlock - 1) / kQuadBlock;
+                          float* xyz, int32_t* tri, uint8_t* cls, int64_t cap_t, uint64_t* masks,
+                          int32_t* block_offsets, int32_t* total) {
+    MeshArgs m;
+    m.depth = depth;
+    m.H = cam.height; m.W = cam.width; m.s = stride; m.R = smooth_radius;
+    m.gh = (cam.height + stride - 1) / stride; m.gw = (cam.width + stride - 1) / stride;
+    m.fx = cam.fx; m.fy = cam.fy; m.cx = cam.cx; m.cy = cam.cy;
+    m.z_min = z_min; m.z_max = z_max;
+    for (int k = 0; k < 12; ++k) m.T.m[k] = T[k];
+    const int64_t nn = (int64_t)m.gh * m.gw;
+    const int64_t nb = meshify_blocks(m.H, m.W, stride);
+    const int bw = (m.gw - 1 + kQuadBlock - 1) / kQuadBlock;
     const double lim2 = (double)max_edge * (double)max_edge;
     if (nb == 0) {
-        hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, total, (int64_t)1);
+        hipLaunchKernelGGL(k_mesh_nodes, dim3((unsigned)((8 * nn + 255) / 256)), dim3(256), 0, st, m, xyz, total);
         return hipGetLastError();
     }
-    const unsigned g = (unsigned)((nb + 3) / 4);
-    hipLaunchKernelGGL(k_mesh_count, dim3(g), dim3(256), 0, st, xyz, kind, gh, gw, bw, nb, lim2, block_counts);
-    hipLaunchKernelGGL(k_mesh_scan, dim3(1), dim3(1024), 0, st, block_counts, nb, block_offsets, total);
-    hipLaunchKernelGGL(k_mesh_emit, dim3(g), dim3(256), 0, st, xyz, kind, gh, gw, bw, nb, lim2, block_offsets,
-                       cap_t, tri, cls);
+    const int patch = kQuadBlock * stride + 2 * smooth_radius + 1;
+    const dim3 grid((unsigned)nb);
+    if (smooth_radius == 0)
+        hipLaunchKernelGGL((k_mesh_block<1, false>), grid, dim3(kWG), 0, st, m, bw, lim2, 0, xyz, masks);
+    else if (patch <= kMaxPatch)
+        hipLaunchKernelGGL((k_mesh_block<8, true>), grid, dim3(kWG), (size_t)patch * patch * sizeof(float), st, m, bw,
+                           lim2, patch, xyz, masks);
+    else
+        hipLaunchKernelGGL((k_mesh_block<8, false>), grid, dim3(kWG), 0, st, m, bw, lim2, 0, xyz, masks);
+    const bool direct = nb <= kDirectBlocks;
+    if (!direct) hipLaunchKernelGGL(k_mesh_scan, dim3(1), dim3(1024), 0, st, masks, nb, block_offsets);
+    hipLaunchKernelGGL(k_mesh_emit, dim3((unsigned)((nb + 3) / 4)), dim3(kWG), 0, st, masks, m.gw, bw, nb,
+                       direct ? nullptr : block_offsets, cap_t, tri, cls, total);
     return hipGetLastError();
 }
 
