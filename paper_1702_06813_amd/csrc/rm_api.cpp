@@ -1030,10 +1030,7 @@ int rm_depth_normals(rm_ctx* ctx, const float* depth, int32_t height, int32_t wi
     }
     for (int k = 0; k <= 2 * radius; ++k) gw.w[k] /= sum;
     DeviceGuard g(ctx->device);
-    int rc = ensure_scratch(ctx, (size_t)height * width * sizeof(double));
-    if (rc) return rc;
-    RM_HIP(ctx, launch_depth_normals(ctx->stream, depth, height, width, (double)fx, (double)fy, gw, at<double>(ctx, 0),
-                                     normals));
+    RM_HIP(ctx, launch_depth_normals(ctx->stream, depth, height, width, (double)fx, (double)fy, gw, normals));
     return RM_OK;
 }
 

@@ -162,9 +162,8 @@ struct GaussW {
 };
 hipError_t launch_downsample(hipStream_t st, const float* depth, int32_t H, int32_t W, int32_t f, float z_max,
                              float* out);
-// smoothed: device scratch [H][W] f64
 hipError_t launch_depth_normals(hipStream_t st, const float* depth, int32_t H, int32_t W, double fx, double fy,
-                                const GaussW& g, double* smoothed, float* normals);
+                                const GaussW& g, float* normals);
 // T_wc: host, 12 doubles
 hipError_t launch_vertex_normals(hipStream_t st, const float* normals, int32_t H, int32_t W, int32_t stride,
                                  const double* T_wc, float* out);
