@@ -180,18 +180,15 @@ const int kTiles[kNumTiles][2] = {{64, 32}, {32, 32}, {16, 16}, {8, 8}};
 void plan(BatchDesc& bd, int tw, int th) {
     bd.tile_w = tw;
     bd.tile_h = th;
-    int64_t items = 0, recs = 0;
+    int64_t recs = 0;
     for (int s = 0; s < bd.n_scans; ++s) {
         ScanDesc& d = bd.s[s];
         d.tiles_x = (d.width + tw - 1) / tw;
         d.tiles_y = (d.height + th - 1) / th;
-        d.item_off = items;
-        d.rec_off = recs;
-        const int64_t n = (int64_t)d.n_poses * d.tiles_x * d.tiles_y;
-        items += n;
-        recs += n;
+        bd.rec_off[s] = recs;
+        recs += (int64_t)d.n_poses * d.tiles_x * d.tiles_y;
     }
-    bd.n_items = items;
+    bd.n_items = recs;
 }
 
 int64_t total_records(const BatchDesc& bd) {
@@ -687,7 +684,7 @@ int rm::align_common(rm_ctx* ctx, const rm_mesh* mesh, const rm_scan* scans, int
         bd.s[s].cls = scans[s].cls;
         bd.s[s].mask = scans[s].mask;
         bd.s[s].color = scans[s].color;
-        bd.s[s].pose_off = pose_off[s];
+        bd.pose_off[s] = pose_off[s];
         bd.s[s].n_poses = pose_off[s + 1] - pose_off[s];
     }
     const int P = pose_off[S];
@@ -976,7 +973,6 @@ int rm_render_depth(rm_ctx* ctx, const rm_mesh* mesh, rm_camera cam, const doubl
     bd.n_poses = n_poses;
     rc = fill_scan(ctx, bd.s[0], cam);
     if (rc) return rc;
-    bd.s[0].pose_off = 0;
     bd.s[0].n_poses = n_poses;
     DeviceGuard g(ctx->device);
     const int tw = ctx->tile_w ? ctx->tile_w : 64, th = ctx->tile_w ? ctx->tile_h : 32;

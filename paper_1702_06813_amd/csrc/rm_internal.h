@@ -37,10 +37,8 @@ struct ScanDesc {
     float fx, fy, cx, cy;
     int32_t width, height;
     float z_near, z_far;
-    int32_t pose_off, n_poses;
+    int32_t n_poses;
     int32_t tiles_x, tiles_y;
-    int64_t item_off;     // first work item of this scan
-    int64_t rec_off;      // first partial record of this scan
 };
 
 struct BatchDesc {
@@ -49,6 +47,12 @@ struct BatchDesc {
     int32_t tile_w, tile_h;
     float color_tol;      // color term: agreement threshold of corresponding pixels
     int64_t n_items;
+    // first pose of each scan, and its first work item = partial record (apart
+    // from the scans: a kernel finds its scan by a binary search over two or
+    // four cache lines; a walk over the scans' own fields, a line each, took
+    // up to 7 us of every launch of a 32-scan call)
+    int32_t pose_off[RM_MAX_SCANS];
+    int64_t rec_off[RM_MAX_SCANS];
     ScanDesc s[RM_MAX_SCANS];
 };
 

@@ -53,6 +53,19 @@ __device__ __forceinline__ float3 cam_contract(const PoseF& P, float x, float y,
     return c;
 }
 
+// Last scan whose offset is at most x (off[0] = 0).
+template <typename T>
+__device__ __forceinline__ int find_scan(const T* off, int n_scans, T x) {
+    int s = 0;
+#pragma unroll
+    for (int step = RM_MAX_SCANS / 2; step > 0; step >>= 1)
+        if (s + step < n_scans && x >= off[s + step]) s += step;
+    return s;
+}
+__device__ __forceinline__ int pose_scan(const BatchDesc& bd, int pose) {
+    return find_scan(bd.pose_off, bd.n_scans, pose);
+}
+
 struct CamF {
     float fx, fy, cx, cy, zn, zf;
     int W, H;
@@ -701,12 +714,6 @@ __device__ __forceinline__ bool edges_hit(const FootEdges& g, const float k[4], 
     return hit;
 }
 
-__device__ __forceinline__ int pose_scan(const BatchDesc& bd, int pose) {
-    int s = 0;
-    while (s + 1 < bd.n_scans && pose >= bd.s[s + 1].pose_off) ++s;
-    return s;
-}
-
 // Workgroups loop over (pose, visible cluster) items; each thread bins its
 // triangle into the (pose, tile) bins its footprint touches.  Tile counts of
 // the two size classes are aggregated in LDS over the cluster's tile
@@ -745,13 +752,14 @@ __global__ void __launch_bounds__(kWG, 6) k_bin(BatchDesc bd, RasterArgs a, int3
     __shared__ unsigned long long band_base;
     const int pose = blockIdx.y;
     const int nvis = a.vis_count[pose];
-    const ScanDesc& sd = bd.s[pose_scan(bd, pose)];
+    const int scan = pose_scan(bd, pose);
+    const ScanDesc& sd = bd.s[scan];
     const CamF cam{sd.fx, sd.fy, sd.cx, sd.cy, sd.z_near, sd.z_far, sd.width, sd.height};
     PoseF P;
     load_pose(a.T_wc + 12 * (int64_t)pose, P);
-    const int pl = pose - sd.pose_off;
+    const int pl = pose - bd.pose_off[scan];
     const int ntile = sd.tiles_x * sd.tiles_y;
-    const int64_t rec0 = sd.rec_off + (int64_t)pl * ntile;
+    const int64_t rec0 = bd.rec_off[scan] + (int64_t)pl * ntile;
     const uint32_t cap = (uint32_t)a.bin_cap;
     const uint32_t cap_b = (uint32_t)a.bin_big_cap, cap_s = cap - cap_b;
     int fs = 0, fb = 0;                        // largest fills this thread reserved (for bin_fill)
@@ -1081,32 +1089,30 @@ __device__ __forceinline__ bool decode_item(const BatchDesc& bd, ItemInfo& it) {
     const int64_t chunk = (int64_t)gridDim.x / 8;
     const int64_t item = (b % 8) * chunk + b / 8;
     if (item >= bd.n_items) return false;
-    int s = 0;
-    while (s + 1 < bd.n_scans && item >= bd.s[s + 1].item_off) ++s;
+    const int s = find_scan(bd.rec_off, bd.n_scans, item);
     const ScanDesc& sd = bd.s[s];
-    const int64_t local = item - sd.item_off;
+    const int64_t local = item - bd.rec_off[s];
     it.scan = s;
     it.slice = 0;
     it.slices = 1;
     it.slot = 0;
     it.tile = (int)(local / sd.n_poses);
     it.pose_local = (int)(local % sd.n_poses);
-    it.pose = sd.pose_off + it.pose_local;
-    it.rec = sd.rec_off + (int64_t)it.pose_local * (sd.tiles_x * sd.tiles_y) + it.tile;
+    it.pose = bd.pose_off[s] + it.pose_local;
+    it.rec = bd.rec_off[s] + (int64_t)it.pose_local * (sd.tiles_x * sd.tiles_y) + it.tile;
     return true;
 }
 
 // Item of a partial-record index (persistent scheduling takes items by record).
 __device__ __forceinline__ void decode_rec(const BatchDesc& bd, int64_t rec, ItemInfo& it) {
-    int s = 0;
-    while (s + 1 < bd.n_scans && rec >= bd.s[s + 1].rec_off) ++s;
+    const int s = find_scan(bd.rec_off, bd.n_scans, rec);
     const ScanDesc& sd = bd.s[s];
-    const int64_t local = rec - sd.rec_off;
+    const int64_t local = rec - bd.rec_off[s];
     const int nt = sd.tiles_x * sd.tiles_y;
     it.scan = s;
     it.pose_local = (int)(local / nt);
     it.tile = (int)(local % nt);
-    it.pose = sd.pose_off + it.pose_local;
+    it.pose = bd.pose_off[s] + it.pose_local;
     it.rec = rec;
 }
 
@@ -1584,8 +1590,7 @@ __global__ void __launch_bounds__(kWG) k_cull(BatchDesc bd, const ClusterBounds*
                                               int32_t* __restrict__ vis_count, int32_t* __restrict__ vis_tris) {
     const int c = blockIdx.x * kWG + threadIdx.x;
     const int pose = blockIdx.y;
-    int s = 0;
-    while (s + 1 < bd.n_scans && pose >= bd.s[s + 1].pose_off) ++s;
+    const int s = pose_scan(bd, pose);
     const ScanDesc& sd = bd.s[s];
     bool visible = false;
     uint32_t rect = 0;
@@ -1760,11 +1765,10 @@ __global__ void __launch_bounds__(kRecFields * kRedSplit) k_reduce(BatchDesc bd,
     __shared__ double part[kRedSplit][kRecFields];
     __shared__ double val[kRecFields];
     const int pose = blockIdx.x;
-    int s = 0;
-    while (s + 1 < bd.n_scans && pose >= bd.s[s + 1].pose_off) ++s;
+    const int s = pose_scan(bd, pose);
     const ScanDesc& sd = bd.s[s];
     const int ntile = sd.tiles_x * sd.tiles_y;
-    const float* r = rec + (sd.rec_off + (int64_t)(pose - sd.pose_off) * ntile) * kRecFields;
+    const float* r = rec + (bd.rec_off[s] + (int64_t)(pose - bd.pose_off[s]) * ntile) * kRecFields;
     const int f = threadIdx.x % kRecFields, j = threadIdx.x / kRecFields;
     if (f <= 10 || (mode != kIcp && f >= 39)) {      // integer fields (counts)
         int64_t acc = 0;
@@ -1868,11 +1872,10 @@ __device__ __forceinline__ int order_bucket(uint32_t fill) { return __clz((int)(
 // tile adjacent), so that each workgroup's run of a bucket keeps neighbouring
 // poses of the same tiles, which read the same triangles, together.
 __device__ __forceinline__ int64_t item_record(const BatchDesc& bd, int64_t item) {
-    int sc = 0;
-    while (sc + 1 < bd.n_scans && item >= bd.s[sc + 1].item_off) ++sc;
+    const int sc = find_scan(bd.rec_off, bd.n_scans, item);
     const ScanDesc& sd = bd.s[sc];
-    const int64_t local = item - sd.item_off;
-    return sd.rec_off + (local % sd.n_poses) * (int64_t)(sd.tiles_x * sd.tiles_y) + local / sd.n_poses;
+    const int64_t local = item - bd.rec_off[sc];
+    return bd.rec_off[sc] + (local % sd.n_poses) * (int64_t)(sd.tiles_x * sd.tiles_y) + local / sd.n_poses;
 }
 
 // Cuts a record into slices if it has too many entries and slots are left;
