@@ -674,6 +674,31 @@ __device__ __forceinline__ bool footprint(const PoseF& P, const CamF& cam, float
     return true;
 }
 
+// Whether a footprint of less than a pixel or so certainly covers no pixel
+// centre, so that its triangle need not be binned: no centre in its box, or
+// one that lies outside an edge.  Coordinates this near the screen are within
+// 0.005 px of the contract's snapped ones, plus the bound on the camera
+// centre's rounding; kCentreMargin leaves three times that.  Half of the
+// triangles of a view meshed at the resolution it is seen at go here.
+constexpr float kCentreMargin = 1.0f / 64.0f;
+__device__ __forceinline__ bool misses_centres(const Foot& f, float area2, float umin, float umax, float vmin,
+                                               float vmax) {
+    const float m = f.m - kBinMargin + kCentreMargin;
+    const float x0 = ceilf(umin - m), x1 = floorf(umax + m), y0 = ceilf(vmin - m), y1 = floorf(vmax + m);
+    if (x0 > x1 || y0 > y1) return umax - umin + vmax - vmin < 4.0f;
+    if (x0 != x1 || y0 != y1 || fabsf(area2) < 1e-3f) return false;
+    bool out = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int j = (i + 1) & 3;
+        const float A = area2 > 0.0f ? f.v[i] - f.v[j] : f.v[j] - f.v[i];
+        const float B = area2 > 0.0f ? f.u[j] - f.u[i] : f.u[i] - f.u[j];
+        const float dx = x0 - f.u[i], dy = y0 - f.v[i];
+        out |= A * dx + B * dy < -m * (fabsf(A) + fabsf(B) + 2.0f * (fabsf(dx) + fabsf(dy)));
+    }
+    return out;
+}
+
 // Edge functions of the footprint polygon for the tile test: tile (tx, ty),
 // its pixel centres widened by the margin, certainly misses the polygon when for
 // some edge A x + B y + K < 0 at x = tx * TW, y = ty * TH (A, B the inward
@@ -792,9 +817,10 @@ __global__ void __launch_bounds__(kWG, 6) k_bin(BatchDesc bd, RasterArgs a, int3
                     area2 += f.u[i] * f.v[j] - f.u[j] * f.v[i];
                 }
                 big = (umax - umin + 4.0f) * (vmax - vmin + 4.0f) > kBigFootprint;
+                const bool empty = misses_centres(f, area2, umin, umax, vmin, vmax);
                 umin -= f.m; vmin -= f.m; umax += f.m; vmax += f.m;
                 const float W1f = (float)(cam.W - 1), H1f = (float)(cam.H - 1);
-                ok = umax >= 0.0f && vmax >= 0.0f && umin <= W1f && vmin <= H1f;
+                ok = !empty && umax >= 0.0f && vmax >= 0.0f && umin <= W1f && vmin <= H1f;
                 if (ok) {
                     tx0 = max((int)fmaxf(umin, 0.0f) / TW, rx0);
                     tx1 = min((int)fminf(umax, W1f) / TW, rx1);
