@@ -292,9 +292,10 @@ class Mesh:
     @staticmethod
     def concat(meshes):
         """Union of meshes (vertex index offsets applied on the device)."""
-        xyz, tri, cls, off = [], [], [], 0
+        xyz, cls, offs, off = [], [], [], 0
         for m in meshes:
-            xyz.append(m.xyz); tri.append(m.tri + off); cls.append(m.cls); off += m.xyz.shape[0]
+            xyz.append(m.xyz); cls.append(m.cls); offs.append(off); off += m.xyz.shape[0]
+        tri = torch._foreach_add([m.tri for m in meshes], offs)      # (one launch for many meshes)
         color = None
         if all(m.color is not None for m in meshes):
             color = torch.cat([m.color for m in meshes]).contiguous()
