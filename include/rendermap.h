@@ -241,7 +241,9 @@ int rm_set_bin_pool(rm_ctx* ctx, int64_t entries);
  *      poses of a tile on one XCD, sharing its L2)
  *   2  persistent: after binning, items are ordered longest first (counting
  *      sort by log2 of their bin fill) and as many workgroups as fit on the
- *      device take the next item from a queue until it is empty
+ *      device take the next item from a queue until it is empty; in calls of
+ *      few items, those with many more triangles than a workgroup's share are
+ *      cut into slices for several workgroups
  * Results do not depend on it (each item writes its own partial record).
  * Returns RM_ERR_INVALID_ARG for other values. */
 int rm_set_schedule(rm_ctx* ctx, int32_t mode);
