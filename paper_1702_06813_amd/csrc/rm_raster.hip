@@ -600,6 +600,7 @@ __device__ __forceinline__ int setup_triangle(uint64_t* keys, WaveQueue& q, int 
 struct Foot {
     float u[4], v[4];      // convex polygon; a triangle repeats its last vertex
     float m;               // margin, px
+    bool whole;            // not clipped
 };
 
 // Base margin: covers the 1/512 px vertex snap, the hardware reciprocal and
@@ -662,6 +663,7 @@ __device__ __forceinline__ bool footprint(const PoseF& P, const CamF& cam, float
     // the polygon's least depth, and |u - c| up to the larger image side.
     // (the hardware reciprocal's relative error, ~2^-22, is far inside the
     // factor 2 of the bound)
+    f.whole = nin == 3;
     const float zmin = fmaxf(fminf(Q0.z, fminf(Q1.z, fminf(Q2.z, Q3.z))), znp);
     const float tn = fabsf(P.tf[0]) + fabsf(P.tf[1]) + fabsf(P.tf[2]);
     f.m = kBinMargin + 0x1p-23f * (tn + 9.0f * dm) * (fmaxf(cam.fx, cam.fy) + (float)max(cam.W, cam.H)) *
@@ -678,8 +680,12 @@ __device__ __forceinline__ bool footprint(const PoseF& P, const CamF& cam, float
 // centre, so that its triangle need not be binned: no centre in its box, or
 // one that lies outside an edge.  Coordinates this near the screen are within
 // 0.005 px of the contract's snapped ones, plus the bound on the camera
-// centre's rounding; kCentreMargin leaves three times that.  Half of the
-// triangles of a view meshed at the resolution it is seen at go here: 256 poses
+// centre's rounding; kCentreMargin leaves three times that.  The edge test
+// needs an area whose sign that error cannot change (at most 2 m (L + m), L the
+// box's width and height), taken from differences of coordinates: a sum of
+// u v' - u' v cancels at full image coordinates and leaves less than that
+// certain.  Clipped polygons stay in: how far a clip point moves has no such
+// bound.  Half of the triangles of a view meshed at the resolution it is seen at go here: 256 poses
 // of 1280x960 against 4 M triangles 8.70 -> 6.82 ms a call (binning 2.65 ->
 // 2.43, rasterizing 5.9 -> 4.23), 64 poses of 640x480 against 1 M unchanged.
 // Looking at up to 2 x 2 centres instead of one gave 6.96 ms.
@@ -688,8 +694,10 @@ __device__ __forceinline__ bool misses_centres(const Foot& f, float area2, float
                                                float vmax) {
     const float m = f.m - kBinMargin + kCentreMargin;
     const float x0 = ceilf(umin - m), x1 = floorf(umax + m), y0 = ceilf(vmin - m), y1 = floorf(vmax + m);
-    if (x0 > x1 || y0 > y1) return umax - umin + vmax - vmin < 4.0f;
-    if (x0 != x1 || y0 != y1 || fabsf(area2) < 1e-3f) return false;
+    const float L = umax - umin + vmax - vmin;
+    if (!f.whole) return false;
+    if (x0 > x1 || y0 > y1) return L < 4.0f;
+    if (x0 != x1 || y0 != y1 || !(fabsf(area2) > 2.0f * m * (L + m))) return false;
     bool out = false;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -814,11 +822,13 @@ __global__ void __launch_bounds__(kWG, 6) k_bin(BatchDesc bd, RasterArgs a, int3
                 float umin = f.u[0], umax = f.u[0], vmin = f.v[0], vmax = f.v[0];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int j = (i + 1) & 3;
                     umin = fminf(umin, f.u[i]); umax = fmaxf(umax, f.u[i]);
                     vmin = fminf(vmin, f.v[i]); vmax = fmaxf(vmax, f.v[i]);
-                    area2 += f.u[i] * f.v[j] - f.u[j] * f.v[i];
                 }
+                // (of differences: sums over image coordinates would cancel)
+                const float eu = f.u[2] - f.u[0], ev = f.v[2] - f.v[0];
+                area2 = ((f.u[1] - f.u[0]) * ev - (f.v[1] - f.v[0]) * eu) +
+                        (eu * (f.v[3] - f.v[0]) - ev * (f.u[3] - f.u[0]));
                 big = (umax - umin + 4.0f) * (vmax - vmin + 4.0f) > kBigFootprint;
                 const bool empty = misses_centres(f, area2, umin, umax, vmin, vmax);
                 umin -= f.m; vmin -= f.m; umax += f.m; vmax += f.m;
