@@ -619,7 +619,13 @@ __device__ __forceinline__ float3 clip_approx(float3 I, float3 O, float zc) {
     return make_float3(fmaf(t, O.x - I.x, I.x), fmaf(t, O.y - I.y, I.y), zc);
 }
 
-__device__ __forceinline__ bool footprint(const PoseF& P, const CamF& cam, float3 W0, float3 W1, float3 W2,
+// Largest |f| + |u - c| of an image (focal lengths may be negative, a mirrored
+// axis; their signs must not shrink the margin).
+__device__ __forceinline__ float margin_reach(const CamF& cam) {
+    return fmaxf(fabsf(cam.fx), fabsf(cam.fy)) + (float)max(cam.W, cam.H);
+}
+
+__device__ __forceinline__ bool footprint(const PoseF& P, const CamF& cam, float reach, float3 W0, float3 W1, float3 W2,
                                           Foot& f) {
     float3 V[3];
     const float3 Wv[3] = {W0, W1, W2};
@@ -660,14 +666,14 @@ __device__ __forceinline__ bool footprint(const PoseF& P, const CamF& cam, float
     // less than 2^-24 (|t| + 9 |d|) (both roundings of the difference, both
     // float32 rotations), which moves the projection of a point of depth z
     // at most (f + |u - c|) / z times as far; bounded here with twice that,
-    // the polygon's least depth, and |u - c| up to the larger image side.
+    // the polygon's least depth, and |u - c| up to the larger image side
+    // (reach = f + |u - c|).
     // (the hardware reciprocal's relative error, ~2^-22, is far inside the
     // factor 2 of the bound)
     f.whole = nin == 3;
     const float zmin = fmaxf(fminf(Q0.z, fminf(Q1.z, fminf(Q2.z, Q3.z))), znp);
     const float tn = fabsf(P.tf[0]) + fabsf(P.tf[1]) + fabsf(P.tf[2]);
-    f.m = kBinMargin + 0x1p-23f * (tn + 9.0f * dm) * (fmaxf(cam.fx, cam.fy) + (float)max(cam.W, cam.H)) *
-                           __builtin_amdgcn_rcpf(zmin);
+    f.m = kBinMargin + 0x1p-23f * (tn + 9.0f * dm) * reach * __builtin_amdgcn_rcpf(zmin);
     proj_approx(cam, Q0, f.u[0], f.v[0]);
     proj_approx(cam, Q1, f.u[1], f.v[1]);
     proj_approx(cam, Q2, f.u[2], f.v[2]);
@@ -791,6 +797,7 @@ __global__ void __launch_bounds__(kWG, 6) k_bin(BatchDesc bd, RasterArgs a, int3
     const int scan = pose_scan(bd, pose);
     const ScanDesc& sd = bd.s[scan];
     const CamF cam{sd.fx, sd.fy, sd.cx, sd.cy, sd.z_near, sd.z_far, sd.width, sd.height};
+    const float reach = uniform(margin_reach(cam));
     PoseF P;
     load_pose(a.T_wc + 12 * (int64_t)pose, P);
     const int pl = pose - bd.pose_off[scan];
@@ -817,7 +824,7 @@ __global__ void __launch_bounds__(kWG, 6) k_bin(BatchDesc bd, RasterArgs a, int3
             const float3 W0 = make_float3(a.xyz[3 * (int64_t)i0], a.xyz[3 * (int64_t)i0 + 1], a.xyz[3 * (int64_t)i0 + 2]);
             const float3 W1 = make_float3(a.xyz[3 * (int64_t)i1], a.xyz[3 * (int64_t)i1 + 1], a.xyz[3 * (int64_t)i1 + 2]);
             const float3 W2 = make_float3(a.xyz[3 * (int64_t)i2], a.xyz[3 * (int64_t)i2 + 1], a.xyz[3 * (int64_t)i2 + 2]);
-            ok = footprint(P, cam, W0, W1, W2, f);
+            ok = footprint(P, cam, reach, W0, W1, W2, f);
             if (ok) {
                 float umin = f.u[0], umax = f.u[0], vmin = f.v[0], vmax = f.v[0];
 #pragma unroll

@@ -1,0 +1,102 @@
+"""The binning margin and the rule that leaves out triangles without a pixel
+centre, for cameras other than the plain pinhole: mirrored axes (negative focal
+lengths).
+
+On the CPU the footprint and the rule are emulated in float32 as the kernel
+computes them; the margin is the base plus
+2^-23 (|t|_1 + 9 max|d|_1) (max(|fx|, |fy|) + max(W, H)) / z_min.  On the GPU a wall
+meshed below the pixel size is rendered away from the world origin, where the
+part of the margin beside its base counts."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from workloads import scenes as S
+
+from test_binning_centres import _covers, _misses
+from test_binning_margin import BASE, _footprint
+
+MIRRORED = S.Camera(-2100.0, -2086.0, 639.5, 479.25, 1280, 960, z_near=0.1, z_far=20.0)
+MIRRORED_TELE = S.Camera(-4200.0, -4200.0, 319.5, 239.5, 640, 480, z_near=0.1, z_far=20.0)
+MIRRORED_X = S.Camera(-1050.0, 1043.0, 639.5, 479.25, 1280, 960, z_near=0.1, z_far=20.0)
+CAMERAS = {"mirrored": MIRRORED, "mirrored_tele": MIRRORED_TELE, "mirrored_x": MIRRORED_X}
+
+
+def _reach(cam):
+    return max(abs(cam.fx), abs(cam.fy)) + max(cam.width, cam.height)
+
+
+def _triangles(cam, scale, n):
+    """n triangles of 0.02 to 4 px on the image of a camera scale metres from the origin, its pose, their float32
+    footprints [n, 3] and the margin beside its base [n]."""
+    rng = np.random.default_rng(11)
+    z = np.exp(rng.uniform(np.log(0.15), np.log(15.0), n))
+    size = np.exp(rng.uniform(np.log(0.02), np.log(4.0), n))
+    c = np.stack([rng.uniform(-2, cam.width + 2, n), rng.uniform(-2, cam.height + 2, n)], 1)
+    c[::3] = np.round(c[::3])                               # many near centres
+    px = c[:, None] + size[:, None, None] * rng.uniform(-0.5, 0.5, (n, 3, 2))
+    zz = z[:, None] * (1 + 0.02 * rng.standard_normal((n, 3)))
+    P = np.stack([(px[..., 0] - cam.cx) / cam.fx * zz, (px[..., 1] - cam.cy) / cam.fy * zz, zz], -1).reshape(-1, 3)
+    T = np.array(S.look_pose(np.array([1.0, -0.7, 0.3]), 0.7, 0.2, 0.1), np.float64)
+    T[:3, 3] += scale * np.array([1.0, -0.7, 0.3])
+    xyz = (P @ T[:3, :3].T + T[:3, 3]).astype(np.float32)
+    mesh = (xyz, np.arange(3 * n, dtype=np.int32).reshape(n, 3), np.zeros(n, np.uint8))
+    Z, u, v, dn, tn = _footprint(xyz, T, cam)
+    Z, u, v, dn = (a.reshape(n, 3) for a in (Z, u, v, dn))
+    m = 2.0 ** -23 * (tn + 9 * dn.max(1)) * _reach(cam) / np.maximum(Z.min(1), cam.z_near)
+    return mesh, T, Z, u, v, m
+
+
+@pytest.mark.parametrize("scale", [0.0, 10.0, 100.0, 1e3, 1e5])
+@pytest.mark.parametrize("name", CAMERAS)
+def test_left_out_triangles_cover_no_centre(name, scale):
+    cam, n = CAMERAS[name], 40000
+    mesh, T, Z, u, v, m = _triangles(cam, scale, n)
+    ok = (Z > cam.z_near * 1.01).all(1)
+    left = np.zeros(n, bool)
+    poly = [0, 1, 2, 2]
+    left[ok] = _misses(u[ok][:, poly], v[ok][:, poly], m[ok] + 1 / 64)
+    sub = O.contract_subtriangles(mesh, cam, T)
+    covering = np.unique(sub[:, 0][_covers(sub[:, 1:])])
+    assert not left[covering].any(), int(left[covering].sum())
+
+
+@pytest.mark.parametrize("scale", [0.0, 10.0, 100.0, 1e3, 1e5])
+@pytest.mark.parametrize("name", CAMERAS)
+def test_margin_covers_contract_vertices(name, scale):
+    cam, n = CAMERAS[name], 40000
+    mesh, T, Z, u, v, m = _triangles(cam, scale, n)
+    sub = O.contract_subtriangles(mesh, cam, T)
+    sub = sub[(Z[sub[:, 0]] > cam.z_near * 1.01).all(1)]    # not clipped: vertices in the mesh's order or with two swapped
+    t = sub[:, 0]
+    X, Y = sub[:, 1::2] / 256.0, sub[:, 2::2] / 256.0
+    d = np.maximum(np.abs(X[:, :, None] - u[t][:, None, :]), np.abs(Y[:, :, None] - v[t][:, None, :])).min(2)
+    on = (X > -1) & (X < cam.width) & (Y > -1) & (Y < cam.height)
+    assert on.any()
+    assert (d - (BASE + m[t])[:, None])[on].max() < 0.0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,cell", [("mirrored", 4.5e-4), ("mirrored_tele", 2.4e-4), ("mirrored_x", 9.5e-4)])
+def test_a_wall_away_from_the_origin_has_no_holes(name, cell):
+    """A tilted wall of right triangles of about a pixel at 1 m, the camera some 120 m from the origin and not at
+    float32 coordinates: every pixel is covered, at the plane's depth (float32 vertices: 1e-6 m in z, 4e-6 m across
+    at a slope below 0.1; 1e-5 m)."""
+    import torch
+    import paper_1702_06813_amd as rm
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    cam = CAMERAS[name]
+    u, v = np.meshgrid(np.arange(cam.width), np.arange(cam.height))
+    rx, ry = (u - cam.cx) / cam.fx, (v - cam.cy) / cam.fy
+    nx, ny = int(2.2 * np.abs(rx).max() / cell), int(2.2 * np.abs(ry).max() / cell)
+    X, Y = np.meshgrid((np.arange(nx + 1) - nx / 2) * cell, (np.arange(ny + 1) - ny / 2) * cell)
+    off = np.array([100.0123456789, -70.0345678912, 30.0567891234])
+    xyz = (np.stack([X, Y, 1.0 + 0.05 * X - 0.03 * Y], -1).reshape(-1, 3) + off).astype(np.float32)
+    q = (np.arange(ny)[:, None] * (nx + 1) + np.arange(nx)).ravel()
+    tri = np.concatenate([np.stack([q, q + 1, q + nx + 1], 1), np.stack([q + 1, q + nx + 2, q + nx + 1], 1)])
+    T = np.concatenate([np.eye(3), off[:, None]], 1).reshape(1, 12)
+    r = rm.render_depth(rm.Mesh.from_arrays(xyz, tri, np.zeros(len(tri), np.uint8)), cam, torch.from_numpy(T).cuda())
+    depth = r["depth"][0].double().cpu().numpy()
+    assert np.isfinite(depth).all(), int((~np.isfinite(depth)).sum())
+    assert np.abs(depth - 1.0 / (1 - 0.05 * rx + 0.03 * ry)).max() < 1e-5
