@@ -620,9 +620,12 @@ __device__ __forceinline__ float3 clip_approx(float3 I, float3 O, float zc) {
 }
 
 // Largest |f| + |u - c| of an image (focal lengths may be negative, a mirrored
-// axis; their signs must not shrink the margin).
+// axis; their signs must not shrink the margin.  A principal point outside the
+// image lies farther from its pixels than the larger image side).
 __device__ __forceinline__ float margin_reach(const CamF& cam) {
-    return fmaxf(fabsf(cam.fx), fabsf(cam.fy)) + (float)max(cam.W, cam.H);
+    const float x = fmaxf(fabsf(cam.cx), fabsf((float)cam.W - cam.cx));
+    const float y = fmaxf(fabsf(cam.cy), fabsf((float)cam.H - cam.cy));
+    return fmaxf(fabsf(cam.fx), fabsf(cam.fy)) + fmaxf((float)max(cam.W, cam.H), fmaxf(x, y));
 }
 
 __device__ __forceinline__ bool footprint(const PoseF& P, const CamF& cam, float reach, float3 W0, float3 W1, float3 W2,
@@ -666,8 +669,7 @@ __device__ __forceinline__ bool footprint(const PoseF& P, const CamF& cam, float
     // less than 2^-24 (|t| + 9 |d|) (both roundings of the difference, both
     // float32 rotations), which moves the projection of a point of depth z
     // at most (f + |u - c|) / z times as far; bounded here with twice that,
-    // the polygon's least depth, and |u - c| up to the larger image side
-    // (reach = f + |u - c|).
+    // the polygon's least depth, and the largest |u - c| of the image (reach).
     // (the hardware reciprocal's relative error, ~2^-22, is far inside the
     // factor 2 of the bound)
     f.whole = nin == 3;

@@ -1,12 +1,13 @@
 """The binning margin and the rule that leaves out triangles without a pixel
 centre, for cameras other than the plain pinhole: mirrored axes (negative focal
-lengths).
+lengths) and principal points far outside the image.
 
 On the CPU the footprint and the rule are emulated in float32 as the kernel
 computes them; the margin is the base plus
-2^-23 (|t|_1 + 9 max|d|_1) (max(|fx|, |fy|) + max(W, H)) / z_min.  On the GPU a wall
-meshed below the pixel size is rendered away from the world origin, where the
-part of the margin beside its base counts."""
+2^-23 (|t|_1 + 9 max|d|_1) (max(|fx|, |fy|) + D) / z_min with D the larger image side
+or, outside the image, the principal point's largest distance from a pixel.
+On the GPU a wall meshed below the pixel size is rendered away from the world
+origin, where the part of the margin beside its base counts."""
 import numpy as np
 import pytest
 
@@ -19,11 +20,15 @@ from test_binning_margin import BASE, _footprint
 MIRRORED = S.Camera(-2100.0, -2086.0, 639.5, 479.25, 1280, 960, z_near=0.1, z_far=20.0)
 MIRRORED_TELE = S.Camera(-4200.0, -4200.0, 319.5, 239.5, 640, 480, z_near=0.1, z_far=20.0)
 MIRRORED_X = S.Camera(-1050.0, 1043.0, 639.5, 479.25, 1280, 960, z_near=0.1, z_far=20.0)
-CAMERAS = {"mirrored": MIRRORED, "mirrored_tele": MIRRORED_TELE, "mirrored_x": MIRRORED_X}
+OFF_IMAGE = S.Camera(60.0, 50.0, 8192.0, 40.0, 160, 120, z_near=0.1, z_far=20.0)
+CROP = S.Camera(525.0, -525.0, -700.0, 1200.0, 640, 480, z_near=0.1, z_far=20.0)
+CAMERAS = {"mirrored": MIRRORED, "mirrored_tele": MIRRORED_TELE, "mirrored_x": MIRRORED_X, "off_image": OFF_IMAGE,
+           "crop": CROP}
 
 
 def _reach(cam):
-    return max(abs(cam.fx), abs(cam.fy)) + max(cam.width, cam.height)
+    return max(abs(cam.fx), abs(cam.fy)) + max(cam.width, cam.height, abs(cam.cx), abs(cam.width - cam.cx), abs(cam.cy),
+                                               abs(cam.height - cam.cy))
 
 
 def _triangles(cam, scale, n):
@@ -61,9 +66,11 @@ def test_left_out_triangles_cover_no_centre(name, scale):
     assert not left[covering].any(), int(left[covering].sum())
 
 
-@pytest.mark.parametrize("scale", [0.0, 10.0, 100.0, 1e3, 1e5])
+# (without its base the margin is that of the left-out triangles: 1/64 px for the snap and the projection instead)
+@pytest.mark.parametrize("base", [BASE, 1 / 64])
+@pytest.mark.parametrize("scale", [0.0, 10.37, 123.456, 1e3, 1e5])
 @pytest.mark.parametrize("name", CAMERAS)
-def test_margin_covers_contract_vertices(name, scale):
+def test_margin_covers_contract_vertices(name, scale, base):
     cam, n = CAMERAS[name], 40000
     mesh, T, Z, u, v, m = _triangles(cam, scale, n)
     sub = O.contract_subtriangles(mesh, cam, T)
@@ -73,7 +80,7 @@ def test_margin_covers_contract_vertices(name, scale):
     d = np.maximum(np.abs(X[:, :, None] - u[t][:, None, :]), np.abs(Y[:, :, None] - v[t][:, None, :])).min(2)
     on = (X > -1) & (X < cam.width) & (Y > -1) & (Y < cam.height)
     assert on.any()
-    assert (d - (BASE + m[t])[:, None])[on].max() < 0.0
+    assert (d - (base + m[t])[:, None])[on].max() < 0.0
 
 
 @pytest.mark.gpu
