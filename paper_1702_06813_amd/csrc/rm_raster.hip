@@ -91,11 +91,15 @@ __device__ __forceinline__ bool snap(const CamF& c, float3 P, int& X, int& Y) {
     return true;
 }
 
-__device__ __forceinline__ uint64_t pack_key(float w, uint32_t id) {
-    // resolved by atomic maximum: nearer surface = larger w = 1/z = larger
-    // key (w >= 0, so its bits order like its value); equal depths: the
-    // lower id has the larger complement and wins
-    return ((uint64_t)__float_as_uint(w) << 32) | (uint64_t)(~id);
+// Offers a fragment to its pixel's key by signed atomic maximum: nearer
+// surface = larger w = 1/z = larger key (for w >= 0 its bits order like its
+// value); equal depths: the lower id has the larger complement and wins.  A
+// fragment with w < 0, behind the camera on a plane seen edge on, is a
+// negative key and loses even to the empty one.  So a pixel's key is the
+// maximum of all fragments with w >= 0, in whatever order they come.
+__device__ __forceinline__ void offer(uint64_t* key, float w, uint32_t id) {
+    const uint64_t k = ((uint64_t)__float_as_uint(w) << 32) | (uint64_t)(~id);
+    atomicMax(reinterpret_cast<long long*>(key), (long long)k);
 }
 constexpr uint64_t kEmptyKey = 0ull;       // w = 0: behind everything
 
@@ -126,13 +130,13 @@ __device__ __forceinline__ PlaneN plane_normal(const PoseF& P, const float v[9])
 }
 
 // 1/z over the image: w(u, v) = a (u - cx) + b (v - cy) + e.
-__device__ __forceinline__ WPlane depth_plane(const PlaneN& q, double ifx, double ify) {
+// False for a plane through the camera centre (c = 0), which has no depth.
+__device__ __forceinline__ bool depth_plane(const PlaneN& q, double ifx, double ify, WPlane& p) {
     const double ic = 1.0 / q.c;
-    WPlane p;
     p.a = q.nx * ic * ifx;
     p.b = q.ny * ic * ify;
     p.e = q.nz * ic;
-    return p;
+    return fabs(ic) < (double)INFINITY;
 }
 
 struct Tile {
@@ -140,9 +144,11 @@ struct Tile {
 };
 
 
-// Occlusion margin: a row of a triangle is skipped when its nearest depth,
-// scaled by this factor, is still farther than the farthest key of the row
-// snapshot (far more than the rounding between the FP64 plane and the f32 key).
+// Occlusion margin: a row of a triangle is skipped when the larger |1/z| of its
+// ends, scaled by this factor, is still farther than the farthest key of the
+// row snapshot (far more than the rounding of the sums along the row and
+// between the FP64 plane and the f32 key; of a row that reaches behind the
+// camera, w < 0, the negative end counts too, as it sets that rounding).
 constexpr double kOccMargin = 1.0 + 1e-6;
 // The depth snapshot keeps one value per kSeg-pixel segment of each tile row
 // (index row * kSegs + x / kSeg) and, from kSnapTile on, the farthest of each
@@ -298,7 +304,7 @@ __device__ __forceinline__ bool exact_steps(double w0, double& pa, double& pb, i
 
 // A triangle of a few pixels, walked by its own lane over its box (int32 edge
 // functions: spans below 2^14).
-__device__ __forceinline__ void raster_tiny(uint64_t* keys, int stride, const float* rmin, const Tile& tl, const int X[3], const int Y[3],
+__device__ __forceinline__ void raster_tiny(uint64_t* keys, int stride, const Tile& tl, const int X[3], const int Y[3],
                                             int px0, int px1, int py0, int py1, const WPlane& pl, double cx, double cy,
                                             uint32_t id) {
     const int area = (X[1] - X[0]) * (Y[2] - Y[0]) - (Y[1] - Y[0]) * (X[2] - X[0]);
@@ -320,14 +326,10 @@ __device__ __forceinline__ void raster_tiny(uint64_t* keys, int stride, const fl
     for (int y = py0; y <= py1; ++y) {
         int e0 = E[0], e1 = E[1], e2 = E[2];
         double w = wrow;
-        // (a row of so few pixels is drawn without a look at the snapshot,
-        // except where a plane seen edge on leaves 1/z negative in the box)
-        const double we = fma(pl.a, (double)(px1 - px0), wrow);
-        const bool skip = fmin(wrow, we) < 0.0 && fmax(wrow, we) * kOccMargin <
-                                                      (double)snap_min(rmin, y - tl.y0, px0 - tl.x0, px1 - tl.x0);
+        // (a row of so few pixels is drawn without a look at the snapshot)
 #pragma unroll 1
-        for (int x = skip ? px1 + 1 : px0; x <= px1; ++x) {
-            if ((e0 | e1 | e2) >= 0) atomicMax((unsigned long long*)(row + x), pack_key((float)w, id));
+        for (int x = px0; x <= px1; ++x) {
+            if ((e0 | e1 | e2) >= 0) offer(row + x, (float)w, id);
             e0 += sx[0]; e1 += sx[1]; e2 += sx[2];
             w += pl.a;
         }
@@ -346,7 +348,7 @@ __device__ __forceinline__ void raster_tiny(uint64_t* keys, int stride, const fl
 // ms a call, 9.32 without; ICP of 32 pairs of 320x240 297 us, 314 without;
 // 640x480 with 1 M triangles within 1.5 %).
 template <int TW>
-__device__ __forceinline__ int emit_tri(uint64_t* keys, WaveQueue& q, int lane, const float* rmin, const Tile& tl, const CamF& cam, float3 A, float3 B,
+__device__ __forceinline__ int emit_tri(uint64_t* keys, WaveQueue& q, int lane, const Tile& tl, const CamF& cam, float3 A, float3 B,
                                         float3 C, const WPlane& pl, uint32_t id) {
     int X[3], Y[3];
     if (!snap(cam, A, X[0], Y[0]) || !snap(cam, B, X[1], Y[1]) || !snap(cam, C, X[2], Y[2])) return 0;
@@ -360,7 +362,7 @@ __device__ __forceinline__ int emit_tri(uint64_t* keys, WaveQueue& q, int lane, 
     uint32_t box = (uint32_t)(px0 - tl.x0) | ((uint32_t)(px1 - tl.x0) << 6) | ((uint32_t)(py0 - tl.y0) << 12) |
                    ((uint32_t)(py1 - tl.y0) << 18);
     if (!__ballot(boxpx > kTinyArea || mxx - mnx >= (1 << 14) || mxy - mny >= (1 << 14))) {
-        raster_tiny(keys, TW + 1, rmin, tl, X, Y, px0, px1, py0, py1, pl, (double)cam.cx, (double)cam.cy, id);
+        raster_tiny(keys, TW + 1, tl, X, Y, px0, px1, py0, py1, pl, (double)cam.cx, (double)cam.cy, id);
         return 0;
     }
     double pa = pl.a, pb = pl.b, w0 = fma(pl.a, (double)px0 - (double)cam.cx, pl.e);
@@ -481,11 +483,12 @@ __device__ __forceinline__ void raster_jobs(uint64_t* keys, WaveQueue& q, const 
             // columns, behind everything visible there changes no key
             const int sa = small ? bx0 : xa, sb = small ? bx1 : xb;
             uint64_t* row = keys + r * (TW + 1);
-            if (xa <= xb && fmax(wt, fma(pa, (double)(sb - sa), wt)) * kOccMargin >= (double)snap_min(rmin, r, sa, sb)) {
+            if (xa <= xb &&
+                fmax(fabs(wt), fabs(fma(pa, (double)(sb - sa), wt))) * kOccMargin >= (double)snap_min(rmin, r, sa, sb)) {
                 // (the loop runs on the key address; the far plane is applied
                 // at the resolve, see there)
                 for (uint64_t *k = row + xa, *kend = row + xb; k <= kend; ++k) {
-                    atomicMax((unsigned long long*)k, pack_key((float)w, id));
+                    offer(k, (float)w, id);
                     w += pa;
                 }
             }
@@ -548,12 +551,12 @@ __device__ __forceinline__ int setup_triangle(uint64_t* keys, WaveQueue& q, int 
     // the round start, no pixel of the triangle can change:
     // (1/z_min + |a| + |b|) (1 + 1e-5) < w_key.  Outside ICP mode the test is
     // taken multiplied by z_min |c| > 0, so that a skipped triangle needs no
-    // division (c = 0, a plane through the camera centre, is never skipped);
+    // division (a plane through the camera centre, c = 0, is left out after it);
     // in ICP mode the plane first (fewer registers live across the test there).
     const float wt = fminf(fminf(rmin[kSnapTile], rmin[kSnapTile + 1]), fminf(rmin[kSnapTile + 2], rmin[kSnapTile + 3]));
     WPlane pl;
     if constexpr (MODE == kIcp) {
-        pl = depth_plane(pn, ifx, ify);
+        if (!depth_plane(pn, ifx, ify, pl)) return 0;
         if (nin == 3) {
             const double wv = 1.0 / (double)fminf(V0.z, fminf(V1.z, V2.z)) + fabs(pl.a) + fabs(pl.b);
             if (wv * 1.00001 < (double)wt) return 0;
@@ -565,7 +568,7 @@ __device__ __forceinline__ int setup_triangle(uint64_t* keys, WaveQueue& q, int 
             const double lhs = (ac + zmin * (fabs(pn.nx) * ifx + fabs(pn.ny) * ify)) * 1.00001;
             if (lhs < (double)wt * zmin * ac) return 0;
         }
-        pl = depth_plane(pn, ifx, ify);
+        if (!depth_plane(pn, ifx, ify, pl)) return 0;
     }
     const uint32_t id = (uint32_t)in.t;
     // near-plane clip into at most two sub-triangles; one emit call site keeps
@@ -588,7 +591,7 @@ __device__ __forceinline__ int setup_triangle(uint64_t* keys, WaveQueue& q, int 
         const float3 b = sel3(k == 0 ? 2 : k - 1, V0, V1, V2);
         A0 = I; B0 = clip_point(I, a, cam.zn); C0 = clip_point(I, b, cam.zn);
     }
-    return emit_tri<TW>(keys, q, lane, rmin, tl, cam, A0, B0, C0, pl, id);
+    return emit_tri<TW>(keys, q, lane, tl, cam, A0, B0, C0, pl, id);
 }
 
 // ------------------------------------------------------------------ binning
