@@ -565,7 +565,7 @@ __device__ __forceinline__ int setup_triangle(uint64_t* keys, WaveQueue& q, int 
         if (nin == 3) {
             const double zmin = (double)fminf(V0.z, fminf(V1.z, V2.z));
             const double ac = fabs(pn.c);
-            const double lhs = (ac + zmin * (fabs(pn.nx) * ifx + fabs(pn.ny) * ify)) * 1.00001;
+            const double lhs = (ac + zmin * (fabs(pn.nx * ifx) + fabs(pn.ny * ify))) * 1.00001;
             if (lhs < (double)wt * zmin * ac) return 0;
         }
         if (!depth_plane(pn, ifx, ify, pl)) return 0;
