@@ -65,6 +65,8 @@ struct rm_ctx {
     // once a graph has been captured, scratch that it may reference is never freed early
     bool captured = false;
     std::vector<void*> retired;
+    // scratch with slots for cut records did not fit on the device: later calls take what room there is
+    bool slots_oom = false;
 };
 
 namespace {
@@ -363,7 +365,10 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
     int32_t* vis_tris = nullptr;
     int32_t* bin_max = nullptr;
     int64_t cap = 0, cap_b = 0;
-    // slices of split records
+    // Slices of split records, at most.  Their list and key slots (kMaxSplit x
+    // 16 KB, 64 MB, for 64x32 tiles) only speed a call up, so it never fails for
+    // them: a fixed buffer, scratch under capture and a device out of memory
+    // give as many slots as they have room for, or none.
     int64_t split_want = persistent && R <= kSplitRecords ? std::min<int64_t>(kMaxSplit, R * kMaxSlices) : 0;
     for (int attempt = 0;; ++attempt) {
         // the capacity learned so far (or fixed), limited to what this call's records may take
@@ -381,7 +386,7 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
         const int64_t n_cnt = 2 * (int64_t)P + 4 + 2 * R + kOrderWords;
         const size_t o_cnt = cv.take<int32_t>(n_cnt);
         const size_t o_ord = cv.take<int32_t>(persistent ? R : 1);
-        const size_t o_split = cv.take<uint4>(n_split);
+        const size_t o_split = n_split > 0 ? cv.take<uint4>(n_split) : 0;
         const size_t o_vis = cv.take<uint2>((int64_t)P * C);
         const size_t o_visz = cv.take<float>((int64_t)P * C);
         const size_t o_rec = cv.take<float>(mode == kRender ? 1 : R * kRecFields);
@@ -396,6 +401,10 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
         const size_t o_spill = spill_cap > 0 ? cv.take<uint3>(spill_cap) : 0;
         const size_t o_pool = pool_cap > 0 ? cv.take<uint32_t>(pool_cap) : 0;
         const size_t o_bin = cv.off;
+        // slots that fit behind the bins in `size` bytes
+        auto slots_in = [&](size_t size) {
+            return std::min<int64_t>(n_split, (int64_t)((size - std::min(size, cv.off)) / ((size_t)tw * th * sizeof(uint64_t))));
+        };
         char* base = nullptr;
         if (arena.fixed) {
             // bins take what the fixed buffer leaves; a bin that overflows a
@@ -409,14 +418,26 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
                                                   "allocation-free buffer holds %zu", o_bin + 256, arena.fixed_size);
             cap = std::min<int64_t>(cap, (int64_t)((arena.fixed_size - o_bin) / 4) / std::max<int64_t>(R, 1));
             cv.take<uint32_t>(R * cap);
-            // slots for split records from what is then left
-            n_split = std::min<int64_t>(n_split, (int64_t)((arena.fixed_size - std::min(arena.fixed_size, cv.off)) /
-                                                           ((size_t)tw * th * sizeof(uint64_t))));
+            n_split = slots_in(arena.fixed_size);
             base = arena.fixed;
         } else {
             cv.take<uint32_t>(R * cap);
-            cv.take<uint64_t>(n_split * tw * th);
+            if (capturing(ctx) || ctx->slots_oom) {
+                if (cv.off > ctx->scratch_size && split_want > 0) {
+                    split_want = 0;
+                    continue;
+                }
+                n_split = slots_in(ctx->scratch_size);
+            }
+            if (n_split > 0) cv.take<uint64_t>(n_split * tw * th);
             int rc = ensure_scratch(ctx, cv.off);
+            if (rc == RM_ERR_OOM && split_want > 0) {
+                ctx->err.clear();
+                ctx->slots_oom = true;         // (and do not try again on every call)
+                split_want = 0;
+                --attempt;                     // (the sizing of the bins has its own attempts)
+                continue;
+            }
             if (rc) return rc;
             base = static_cast<char*>(ctx->scratch);
         }
