@@ -40,7 +40,9 @@ __global__ void __launch_bounds__(kWG) k_depth_normals(const float* __restrict__
     __shared__ float z[kNrmPH * kNrmPW];
     __shared__ double zs[(kNrmH + 2) * (kNrmW + 2)];
     static_assert(kNrmW * kNrmH == kWG, "a thread per normal");
-    const int bx = blockIdx.x * kNrmW, by = blockIdx.y * kNrmH;
+    // (blocks of all rows in one grid dimension: images may be taller than the others reach)
+    const unsigned nbx = (unsigned)(W + kNrmW - 1) / kNrmW;
+    const int bx = (int)(blockIdx.x % nbx) * kNrmW, by = (int)(blockIdx.x / nbx) * kNrmH;
     const float q = __int_as_float(0x7fc00000);
     const int pw = kNrmW + 2 * (R + 1), ph = kNrmH + 2 * (R + 1), ox = bx - R - 1, oy = by - R - 1;
     for (int p = threadIdx.x; p < pw * ph; p += kWG) {
@@ -117,7 +119,7 @@ hipError_t launch_downsample(hipStream_t st, const float* depth, int32_t H, int3
 
 hipError_t launch_depth_normals(hipStream_t st, const float* depth, int32_t H, int32_t W, double fx, double fy,
                                 const GaussW& g, float* normals) {
-    const dim3 grid((unsigned)((W + kNrmW - 1) / kNrmW), (unsigned)((H + kNrmH - 1) / kNrmH));
+    const dim3 grid((unsigned)((W + kNrmW - 1) / kNrmW) * (unsigned)((H + kNrmH - 1) / kNrmH));
 #define RM_NRM(R)                                                                                                  \
     case R: hipLaunchKernelGGL(k_depth_normals<R>, grid, dim3(kWG), 0, st, depth, H, W, g, fx, fy, normals); break;
     static_assert(RM_MAX_NORMAL_RADIUS == 8, "a kernel per radius");
