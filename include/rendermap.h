@@ -258,9 +258,9 @@ int rm_set_schedule(rm_ctx* ctx, int32_t mode);
  * launch shape (scans, poses, triangles and clusters, tile, tile records,
  * schedule, bin capacity and its large part with the largest fills,
  * overflow list and region entries with what the spilling bins asked for,
- * scratch bytes) with any growth of the bins or the overflow; with RM_LOG
- * set, that call reads the fills back even where capacity and overflow are
- * fixed. */
+ * slice slots that cut records ask for and that there are, scratch bytes) with
+ * any growth of the bins or the overflow; with RM_LOG set, that call reads the
+ * fills back even where capacity and overflow are fixed. */
 int rm_autotune(rm_ctx* ctx, int32_t enable);
 /* Current tile choice for a single-scan shape (after autotuning), for
  * reporting: the explicit tile, else the tuned one, else 64x32. */

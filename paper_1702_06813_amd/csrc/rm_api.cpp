@@ -224,7 +224,8 @@ std::string tile_limit(const BatchDesc& bd0, int tw, int th) {
 constexpr int64_t kMinBinCap = 64;                     // the budget never shrinks a bin below this
 
 // Pinned readback slots: [1] and [4] largest small and large bin of the last
-// call, [2..3] largest small and large fills of a sizing pass; int64 pairs:
+// call, [2..3] largest small and large fills of a sizing pass, [5] slices that
+// its cut records ask for (read for the log only); int64 pairs:
 // [6..7] and [12..13] list and region entries the last call asked for,
 // [8..9], [10..11] and [14..15] list entries, records and region entries of a
 // sizing pass.
@@ -527,6 +528,9 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
                                    ctx->stream));
         RM_HIP(ctx, hipMemcpyAsync(ctx->pinned + 14, a.spill_top + 4, sizeof(int64_t), hipMemcpyDeviceToHost,
                                    ctx->stream));
+        if (log && persistent)
+            RM_HIP(ctx, hipMemcpyAsync(ctx->pinned + 5, a.queue + 1, sizeof(int32_t), hipMemcpyDeviceToHost,
+                                       ctx->stream));
         RM_HIP(ctx, hipStreamSynchronize(ctx->stream));
         ctx->bin_checked.insert(shape);
         const int64_t fs = ctx->pinned[2], fb = ctx->pinned[3];
@@ -536,11 +540,13 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
                     "[rendermap] plan: %d scans, %d poses, %lld triangles (%lld clusters), tile %dx%d, %lld tile "
                     "records, %s schedule, bin capacity %lld (%lld for large footprints; largest fills %lld "
                     "small, %lld large), overflow list %lld and regions %lld entries (%lld bins spill; they need "
-                    "%lld list and %lld region entries), %zu bytes of scratch\n",
+                    "%lld list and %lld region entries), cut records ask for %d of %lld slice slots, %zu bytes of "
+                    "scratch\n",
                     bd.n_scans, P, (long long)mesh->n_tris, (long long)C, tw, th, (long long)R,
                     persistent ? "persistent longest-first" : "one workgroup per item", (long long)cap,
                     (long long)cap_b, (long long)fs, (long long)fb, (long long)a.spill_cap, (long long)a.pool_cap,
-                    (long long)spill_recs, (long long)spilled, (long long)filled, cv.off);
+                    (long long)spill_recs, (long long)spilled, (long long)filled, persistent ? ctx->pinned[5] : 0,
+                    (long long)n_split, cv.off);
         if ((fs <= cap - cap_b && fb <= cap_b) || attempt >= 2) break;
         if (!fixed_cap && learn_bins(ctx, R, fs, fb)) {
             const int64_t c2 = call_cap(ctx, R), b2 = big_part(ctx, c2);
