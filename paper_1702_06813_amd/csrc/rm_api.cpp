@@ -383,7 +383,7 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
         const bool track = !arena.fixed && (check || ctx->pool_mode > 0 || shape_track);
         Carve cv;
         int64_t n_split = split_want;
-        // vis_count, vis_tris, bin_max[2], bin_fill[2], bin fills, order histogram and cursors, queue[2]
+        // vis_count, vis_tris, bin_max[2], bin_fill[2], bin fills, order histogram and cursors, queue[3]
         const int64_t n_cnt = 2 * (int64_t)P + 4 + 2 * R + kOrderWords;
         const size_t o_cnt = cv.take<int32_t>(n_cnt);
         const size_t o_ord = cv.take<int32_t>(persistent ? R : 1);

@@ -1899,21 +1899,28 @@ hipError_t launch_bin_shape(hipStream_t st, const BatchDesc& bd, const RasterArg
 
 constexpr int kOrderBuckets = 32;
 
-// Share of a workgroup: the call's entries over its resident workgroups.  A
-// record with more entries than that (and kMinSlice) is cut into slices of
-// about that many, so that few or uneven tiles still fill the device: one pose
-// of 640x480 is 150 records whose fullest one used to set the time (350 us of
-// rasterizing; 164 and 24 us of merging in slices).  A slice starts with an
-// empty z-buffer and culls less than the whole record would (1.4 times the
-// instructions there), so records below the share stay whole; slices of half
-// the share made 32 ICP pairs slower (329 against 287 us a call) and one pose
-// no faster.  Calls of more than kSplitRecords records have enough of them.
+// Share of a workgroup: the call's entries over its resident workgroups, at
+// least kMinSlice.  Where the fullest record holds kCutAbove shares, records
+// above the share are cut into slices of about that many entries, so that few
+// or uneven tiles still fill the device: one pose of 640x480 is 150 records
+// whose fullest one used to set the time (350 us of rasterizing; 164 and 24 us
+// of merging in slices).  A slice starts with an empty z-buffer and culls less
+// than the whole record would (1.4 times the instructions there), so cutting
+// does not pay where whole records fill most of the device.  Calls against 1 M
+// triangles, cut and whole: 249 and 433 us with 26 shares in the fullest record
+// (one pose), 421 and 523 us with 6.4 (four), 580 and 566 us with 4.1 (six),
+// 651 and 610 us with 3.1 (eight); 16 ICP pairs with 2.9 shares 164 and 133 us;
+// light calls pay the merge longer (one to four poses of 150,000 entries each,
+// 9 to 10 shares, 1 to 6 % more).  Slices of half the share made 32 ICP pairs
+// slower (329 against 287 us a call) and one pose no faster.
 constexpr int kMinSlice = 2 * kWG;
+constexpr int kCutAbove = 6;
 
-// hist: [0, 32) bucket counts, [32, 64) cursors; a.queue[0] while the order is
-// made: entries of the call in units of 64
-__device__ __forceinline__ uint32_t slice_size(uint32_t total64, int resident) {
-    return (uint32_t)max((int64_t)kMinSlice, (int64_t)total64 * 64 / resident);
+// hist: [0, 32) bucket counts, [32, 64) cursors; while the order is made,
+// a.queue[0]: entries of the call in units of 64, a.queue[2]: the fullest record
+__device__ __forceinline__ uint32_t slice_size(uint32_t total64, uint32_t fullest, int resident) {
+    const uint32_t size = (uint32_t)max((int64_t)kMinSlice, (int64_t)total64 * 64 / resident);
+    return fullest >= (uint64_t)kCutAbove * size ? size : 0xffffffffu;
 }
 
 // bucket 0 holds the costliest records: 31 - floor(log2(fill + 1))
@@ -1971,12 +1978,13 @@ __global__ void __launch_bounds__(kOrderWG) k_order_one(BatchDesc bd, const int3
                                                         int32_t* __restrict__ bin_max) {
     __shared__ int cnt[kOrderBuckets], cur[kOrderBuckets], slots;
     __shared__ uint32_t total;
+    __shared__ int fullest;
     const int tid = threadIdx.x;
     if (tid < kOrderBuckets) cnt[tid] = 0;
-    if (tid == 0) { slots = 0; total = 0; }
+    if (tid == 0) { slots = 0; total = 0; fullest = 0; }
     __syncthreads();
     uint32_t sum = 0;
-    int ms = 0, mb = 0;
+    int ms = 0, mb = 0, mf = 0;
     for (int i0 = 0; i0 < n; i0 += kOrderWG) {
         const int r = i0 + tid;
         const bool live = r < n;
@@ -1984,14 +1992,17 @@ __global__ void __launch_bounds__(kOrderWG) k_order_one(BatchDesc bd, const int3
         const uint32_t fill = (uint32_t)fs + (uint32_t)fb;
         ms = max(ms, fs);
         mb = max(mb, fb);
+        mf = max(mf, (int)fill);
         sum += (fill + 63) >> 6;
         bucket_place(cnt, order_bucket(fill), live);
     }
     sum = (uint32_t)wave_scan_add((int)sum);
     ms = wave_scan_max(ms);
     mb = wave_scan_max(mb);
+    mf = wave_scan_max(mf);
     if ((tid & 63) == 63) {
         atomicAdd(&total, sum);
+        atomicMax(&fullest, mf);
         atomicMax(bin_max, ms);
         atomicMax(bin_max + 1, mb);
     }
@@ -2002,7 +2013,7 @@ __global__ void __launch_bounds__(kOrderWG) k_order_one(BatchDesc bd, const int3
         if (tid < kOrderBuckets) cur[tid] = inc - c;
     }
     __syncthreads();
-    const uint32_t size = slice_size(total, resident);
+    const uint32_t size = slice_size(total, (uint32_t)fullest, resident);
     for (int i0 = 0; i0 < n; i0 += kOrderWG) {
         const int item = i0 + tid;
         const bool live = item < n;
@@ -2018,23 +2029,26 @@ __global__ void __launch_bounds__(kOrderWG) k_order_one(BatchDesc bd, const int3
 __global__ void __launch_bounds__(kWG) k_order_count(const int32_t* __restrict__ bs, const int32_t* __restrict__ bb,
                                                      int64_t n, int32_t* __restrict__ hist, int32_t* __restrict__ queue,
                                                      int32_t* __restrict__ bin_max) {
-    __shared__ int h[kOrderBuckets], sum, top[2];
+    __shared__ int h[kOrderBuckets], sum, top[3];
     if (threadIdx.x < kOrderBuckets) h[threadIdx.x] = 0;
-    if (threadIdx.x == 0) { sum = 0; top[0] = 0; top[1] = 0; }
+    if (threadIdx.x == 0) { sum = 0; top[0] = 0; top[1] = 0; top[2] = 0; }
     __syncthreads();
     const int64_t r = (int64_t)blockIdx.x * kWG + threadIdx.x;
     const int fs = r < n ? bs[r] : 0, fb = r < n ? bb[r] : 0;
     const uint32_t fill = (uint32_t)fs + (uint32_t)fb;
     if (r < n) atomicAdd(&h[order_bucket(fill)], 1);
-    const int ws = wave_scan_add((int)((fill + 63) >> 6)), ms = wave_scan_max(fs), mb = wave_scan_max(fb);
+    const int ws = wave_scan_add((int)((fill + 63) >> 6)), ms = wave_scan_max(fs), mb = wave_scan_max(fb),
+              mf = wave_scan_max((int)fill);
     if ((threadIdx.x & 63) == 63) {
         atomicAdd(&sum, ws);
         atomicMax(&top[0], ms);
         atomicMax(&top[1], mb);
+        atomicMax(&top[2], mf);
     }
     __syncthreads();
     if (threadIdx.x == 0 && sum) atomicAdd(queue, sum);
     if (threadIdx.x < 2 && top[threadIdx.x]) atomicMax(bin_max + threadIdx.x, top[threadIdx.x]);
+    if (threadIdx.x == 2 && top[2]) atomicMax(queue + 2, top[2]);
     if (threadIdx.x < kOrderBuckets && h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
 }
 
@@ -2047,7 +2061,7 @@ __global__ void k_order_offsets(int32_t* hist, int32_t* queue, int resident) {
         hist[kOrderBuckets + k] = acc;
         acc += hist[k];
     }
-    hist[0] = (int32_t)slice_size((uint32_t)queue[0], resident);
+    hist[0] = (int32_t)slice_size((uint32_t)queue[0], (uint32_t)queue[2], resident);
     queue[0] = 0;
 }
 

@@ -23,7 +23,9 @@ def _setup(n_away):
     scan = rm.scan_image(torch.from_numpy(w.scan_depth).cuda(), cam=w.cam)
     away = np.array(w.poses[0], np.float64).reshape(3, 4).copy()
     away[:, 3] += 1000.0
-    poses = np.concatenate([away.reshape(1, 12).repeat(n_away, 0), np.asarray(w.poses[:1]).reshape(1, 12)])
+    back = np.array(w.poses[0], np.float64).reshape(3, 4).copy()
+    back[:, 3] -= 6.0 * back[:, 2]
+    poses = np.concatenate([away.reshape(1, 12).repeat(n_away, 0), back.reshape(1, 12)])
     return rm, w, mesh, scan, torch.from_numpy(np.ascontiguousarray(poses)).cuda()
 
 
@@ -35,8 +37,8 @@ def _slots(capfd):
 
 
 # 640x480: 1,200 tiles of 16x16, 300 of 32x32, 150 of 64x32
-@pytest.mark.parametrize("tile,n_away", [((16, 16), 2), ((16, 16), 5), ((32, 32), 9), ((32, 32), 10), ((64, 32), 20),
-                                         ((64, 32), 53)])
+@pytest.mark.parametrize("tile,n_away", [((16, 16), 0), ((16, 16), 2), ((16, 16), 5), ((32, 32), 9), ((32, 32), 10),
+                                         ((64, 32), 19), ((64, 32), 20), ((64, 32), 53)])
 def test_cut_records_of_large_calls(tile, n_away, capfd, monkeypatch):
     rm, w, mesh, scan, T = _setup(n_away)
     from paper_1702_06813_amd import rendermap
@@ -44,6 +46,7 @@ def test_cut_records_of_large_calls(tile, n_away, capfd, monkeypatch):
     monkeypatch.setenv("RM_LOG", "1")
     ctx = rm.context()
     ctx.set_tile(*tile)
+    vn = torch.nn.functional.normalize(torch.randn(mesh.xyz.shape, generator=torch.Generator().manual_seed(3))).cuda()
     got = {}
     for schedule in (1, 0, 0):
         ctx.set_schedule(schedule)
@@ -56,7 +59,8 @@ def test_cut_records_of_large_calls(tile, n_away, capfd, monkeypatch):
         else:
             assert 0 < asked <= there
         r = rm.render_depth(mesh, w.cam, T)
-        now += [rm.align_cost(mesh, scan, T, EPS), r["tri"], r["depth"].view(torch.int32)]
+        now += [rm.align_cost(mesh, scan, T, EPS), rm.icp_cost_grad(mesh, scan, T, vn), r["tri"],
+                r["depth"].view(torch.int32)]
         for k, x in enumerate(now):
             assert torch.equal(x, got.setdefault(k, x.clone())), (schedule, k)
 
