@@ -358,7 +358,8 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
     const auto shape = std::make_tuple(R, tw, th, mesh->n_tris, P);
     const bool pool_adaptive = ctx->pool_mode < 0 && !arena.fixed;
     const bool log = getenv("RM_LOG") != nullptr;  // the sizing pass then also reports fixed settings
-    const bool check = !arena.fixed && !capturing(ctx) && ctx->bin_checked.count(shape) == 0 &&
+    const bool in_capture = capturing(ctx);
+    const bool check = !arena.fixed && !in_capture && ctx->bin_checked.count(shape) == 0 &&
                        (!fixed_cap || pool_adaptive || log);
     const bool persistent = ctx->schedule != 1;
     RasterArgs a;
@@ -423,7 +424,7 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
             base = arena.fixed;
         } else {
             cv.take<uint32_t>(R * cap);
-            if (capturing(ctx) || ctx->slots_oom) {
+            if (in_capture || ctx->slots_oom) {
                 if (cv.off > ctx->scratch_size && split_want > 0) {
                     split_want = 0;
                     continue;
@@ -585,7 +586,7 @@ int run_pass(rm_ctx* ctx, const rm_mesh* mesh, BatchDesc& bd, int tw, int th, in
     }
     RM_HIP(ctx, launch_raster(ctx->stream, bd, a, mode));
     if (pe1) RM_HIP(ctx, hipEventRecord(pe1, ctx->stream));
-    const bool readback = !capturing(ctx) && !ctx->bin_pending && !arena.fixed;
+    const bool readback = !in_capture && !ctx->bin_pending && !arena.fixed;
     Readback rb;
     if (readback) {
         rb.host = ctx->pinned;
