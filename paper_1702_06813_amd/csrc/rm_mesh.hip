@@ -97,7 +97,7 @@ constexpr int kNodeSide = kQuadBlock + 1;
 
 // PATCH: the windows of the block's nodes, patch x patch pixels, are staged in
 // LDS first (dynamic, patch^2 floats).
-constexpr int kMaxPatch = 88;              // 30 KB: stride 8 with R = 11, stride 6 with R = 19
+constexpr int kMaxPatch = 88;              // 30 KB: stride 8 with R = 11, stride 7 with R = 15
 
 template <int G, bool PATCH>
 __global__ void __launch_bounds__(kWG) k_mesh_block(MeshArgs m, int bw, double lim2, int patch,

@@ -56,6 +56,7 @@ __device__ __forceinline__ float3 cam_contract(const PoseF& P, float x, float y,
 // Last scan whose offset is at most x (off[0] = 0).
 template <typename T>
 __device__ __forceinline__ int find_scan(const T* off, int n_scans, T x) {
+    static_assert((RM_MAX_SCANS & (RM_MAX_SCANS - 1)) == 0, "steps of powers of two");
     int s = 0;
 #pragma unroll
     for (int step = RM_MAX_SCANS / 2; step > 0; step >>= 1)
@@ -217,13 +218,13 @@ __device__ __forceinline__ float snap_min(const float* rmin, int y, int x0, int 
 // queue, and the wave deals the rows of all of them out to its lanes, 64 at a
 // time.  Waves meet at no barrier before the resolve: the z-buffer only takes
 // maxima, and a depth snapshot of any age is a valid bound.  The pass is bound
-// by VALU issue (84 % of the rate on 64 poses of 640x480 against 1 M
-// triangles, 73 % of the lanes active), so what counts is instructions per
+// by VALU issue (86 % of the rate on 64 poses of 640x480 against 1 M
+// triangles, 72 % of the lanes active), so what counts is instructions per
 // row and per triangle.  Before, a workgroup of 256 took rounds of 256
 // triangles with three barriers each, triangles of up to 64 px walked by their
 // own lane (three lanes of a wave busy on average) and larger ones queued as
-// two-row jobs with int64 edge tests: 60 % of the lanes active, 2.48 ms a
-// launch against 1.89 ms now.  Jobs of one row beat jobs of two (1.0 %) and
+// two-row jobs with int64 edge tests: 60 % of the lanes active, 2.06 ms a
+// launch against 1.55 ms now.  Jobs of one row beat jobs of two (1.0 %) and
 // four (4 %).
 //
 // A row's covered span is exact without an edge test per pixel.  With the
@@ -691,14 +692,17 @@ __device__ __forceinline__ bool footprint(const PoseF& P, const CamF& cam, float
 // centre, so that its triangle need not be binned: no centre in its box, or
 // one that lies outside an edge.  Coordinates this near the screen are within
 // 0.005 px of the contract's snapped ones, plus the bound on the camera
-// centre's rounding; kCentreMargin leaves three times that.  The edge test
-// needs an area whose sign that error cannot change (at most 2 m (L + m), L the
-// box's width and height), taken from differences of coordinates: a sum of
-// u v' - u' v cancels at full image coordinates and leaves less than that
-// certain.  Clipped polygons stay in: how far a clip point moves has no such
-// bound.  Half of the triangles of a view meshed at the resolution it is seen at go here: 256 poses
-// of 1280x960 against 4 M triangles 8.70 -> 6.82 ms a call (binning 2.65 ->
-// 2.43, rasterizing 5.9 -> 4.23), 64 poses of 640x480 against 1 M unchanged.
+// centre's rounding, itself twice what can occur; with kCentreMargin in place
+// of the 0.005 px no vertex moves by more than m / 2.  The edge test needs an
+// area whose sign that cannot change: twice the area moves by at most
+// 2 m (L + m), L the box's width and height, and is taken from differences of
+// coordinates, as a sum of u v' - u' v cancels at full image coordinates and
+// leaves less than that certain.  Clipped polygons stay in: how far a clip
+// point moves has no such bound.  Half of the triangles of a view meshed at
+// the resolution it is seen at go here: 256 poses of 1280x960 against 4 M
+// triangles 8.70 -> 6.82 ms a call (binning 2.65 -> 2.43, rasterizing 5.9 ->
+// 4.23).  Where triangles are larger than a pixel it finds little: 64 poses of
+// 640x480 against 1 M triangles bin in 3 % more time, the call unchanged.
 // Looking at up to 2 x 2 centres instead of one gave 6.96 ms.
 constexpr float kCentreMargin = 1.0f / 64.0f;
 __device__ __forceinline__ bool misses_centres(const Foot& f, float area2, float umin, float umax, float vmin,
