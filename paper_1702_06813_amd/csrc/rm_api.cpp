@@ -958,10 +958,12 @@ int rm_mesh_from_range(rm_ctx* ctx, const float* depth, rm_camera cam, const dou
     Carve cv;
     const size_t o_mask = cv.take<uint64_t>(2 * nb);
     const size_t o_off = cv.take<int32_t>(nb);
+    const size_t o_kind = cv.take<uint8_t>(nn);
     rc = ensure_scratch(ctx, cv.off);
     if (rc) return rc;
     RM_HIP(ctx, launch_meshify(ctx->stream, depth, cam, T_wc, stride, smooth_radius, z_min, z_max, max_edge, xyz_out, tri_out,
-                               cls_out, cap_t, at<uint64_t>(ctx, o_mask), at<int32_t>(ctx, o_off), ctx->pinned));
+                               cls_out, cap_t, at<uint64_t>(ctx, o_mask), at<uint8_t>(ctx, o_kind),
+                               at<int32_t>(ctx, o_off), ctx->pinned));
     RM_HIP(ctx, hipStreamSynchronize(ctx->stream));
     *n_v_out = nn;
     *n_t_out = ctx->pinned[0];

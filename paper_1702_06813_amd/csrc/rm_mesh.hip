@@ -43,14 +43,14 @@ struct MeshArgs {
     Pose12 T;
 };
 
-// at(y, x): the depth image's pixel.
-template <int G, typename At>
-__device__ __forceinline__ int mesh_node(const MeshArgs& m, At at, int i, int j, int sub, float out[3]) {
+// WIN: depths are averaged over the window.
+template <int G, bool WIN>
+__device__ __forceinline__ int mesh_node(const MeshArgs& m, int i, int j, int sub, float out[3]) {
     const int py = i * m.s, px = j * m.s;
-    const float z = at(py, px);
+    const float z = m.depth[(int64_t)py * m.W + px];
     const int k = range_class(z, m.z_min, m.z_max);
     double zd = (k == kNoReturn) ? (double)m.z_max : (double)z;
-    if (G > 1) {
+    if (WIN) {
         const double zc = (double)z, tol = RM_SMOOTH_REL * zc;
         double sum = 0.0;
         int cnt = 0;
@@ -59,7 +59,7 @@ __device__ __forceinline__ int mesh_node(const MeshArgs& m, At at, int i, int j,
                 const int x1 = min(px + m.R, m.W - 1);
 #pragma unroll 4
                 for (int xx = max(px - m.R, 0); xx <= x1; ++xx) {
-                    const float zn = at(yy, xx);
+                    const float zn = m.depth[(int64_t)yy * m.W + xx];
                     // (valid, without branches; NaN fails every test)
                     const bool in = (zn > 0.0f) & (zn >= m.z_min) & (zn <= m.z_max) & (fabs((double)zn - zc) <= tol);
                     sum += in ? (double)zn : 0.0;
@@ -83,61 +83,52 @@ __device__ __forceinline__ int mesh_node(const MeshArgs& m, At at, int i, int j,
     return k;
 }
 
-// One workgroup per 8x8 block of quads: the nodes of its 9x9 corners (a corner
-// on a shared side is computed by each block that needs it and written by the
-// one to its lower right), then a wave classifies the quads, lane = row*8 +
-// col.  Quad (qi, qj) between nodes (qi,qj) (qi,qj+1) (qi+1,qj) (qi+1,qj+1)
-// is dropped with a dead corner, free-unknown with a no-return corner or a
-// side beyond the limit, else free-occupied.  masks[2 blk] = quads kept,
-// masks[2 blk + 1] = free-unknown ones.  Latency sets the time: a 160x120 grid
-// with 9x9 windows takes 12 us here; a lane per node and launches of their own
-// for nodes and quads took 25 us, on 75 workgroups, window pixels read from
-// memory instead of LDS 15 us.
+// Quad between the nodes c[0..3] in perimeter order: dropped (keep = false) with
+// a dead corner, free-unknown (fu) with a no-return corner or a side beyond the
+// limit.  kind(n), pos(n): a node's class and world position.
+template <typename I, typename Kind, typename Pos>
+__device__ __forceinline__ void quad_test(const I (&c)[4], Kind kind, Pos pos, double lim2, bool& keep, bool& fu) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int kk = kind(c[k]);
+        keep &= kk != kDead;
+        fu |= kk == kNoReturn;
+        const float* p = pos(c[k]);
+        const float* q = pos(c[(k + 1) & 3]);
+        const double dx = (double)p[0] - (double)q[0];
+        const double dy = (double)p[1] - (double)q[1];
+        const double dz = (double)p[2] - (double)q[2];
+        fu |= ((dx * dx + dy * dy) + dz * dz) > lim2;
+    }
+}
+
+// Nodes without windows: one workgroup per 8x8 block of quads computes the
+// nodes of its 9x9 corners (a corner on a shared side is computed by each block
+// that needs it and written by the one to its lower right), then a wave
+// classifies the quads, lane = row*8 + col.  masks[2 blk] = quads kept,
+// masks[2 blk + 1] = free-unknown ones.  Latency sets the time of small grids,
+// and one launch less counts: a view of 300 blocks takes 31 us whole, 33 us
+// with launches of their own for nodes and quads.
 constexpr int kNodeSide = kQuadBlock + 1;
 
-// PATCH: the windows of the block's nodes, patch x patch pixels, are staged in
-// LDS first (dynamic, patch^2 floats).
-constexpr int kMaxPatch = 88;              // 30 KB: stride 8 with R = 11, stride 7 with R = 15
-
-template <int G, bool PATCH>
-__global__ void __launch_bounds__(kWG) k_mesh_block(MeshArgs m, int bw, double lim2, int patch,
-                                                    float* __restrict__ xyz, uint64_t* __restrict__ masks) {
-    extern __shared__ float stage[];
+__global__ void __launch_bounds__(kWG) k_mesh_block(MeshArgs m, int bw, double lim2, float* __restrict__ xyz,
+                                                    uint64_t* __restrict__ masks) {
     __shared__ float v[kNodeSide * kNodeSide][3];
     __shared__ int kind[kNodeSide * kNodeSide];
+    constexpr int kNodes = kNodeSide * kNodeSide;
+    static_assert(kNodes <= kWG, "a thread per node");
     const int blk = blockIdx.x;
     const int i0 = blk / bw * kQuadBlock, j0 = blk % bw * kQuadBlock;
-    constexpr int kNodes = kNodeSide * kNodeSide, kPer = kWG / G;
-    const int y0 = max(i0 * m.s - m.R, 0), x0 = max(j0 * m.s - m.R, 0);
-    if (PATCH) {
-        for (int p = threadIdx.x; p < patch * patch; p += kWG) {
-            const int y = y0 + p / patch, x = x0 + p % patch;
-            if (y < m.H && x < m.W) stage[p] = m.depth[(int64_t)y * m.W + x];
-        }
-        __syncthreads();
-    }
-    auto at = [&](int y, int x) {
-        return PATCH ? stage[(y - y0) * patch + x - x0] : m.depth[(int64_t)y * m.W + x];
-    };
-    for (int n0 = 0; n0 < kNodes; n0 += kPer) {
-        const int n = n0 + threadIdx.x / G, sub = threadIdx.x % G;
-        const int a = n / kNodeSide, b = n % kNodeSide, i = i0 + a, j = j0 + b;
+    const int n = threadIdx.x, na = n / kNodeSide, nb = n % kNodeSide, i = i0 + na, j = j0 + nb;
+    if (n < kNodes && i < m.gh && j < m.gw) {
         float p[3];
-        int k = kDead;
-        const bool node = n < kNodes && i < m.gh && j < m.gw;
-        // (whole groups of G lanes share n, so a group takes this branch together)
-        if (node) k = mesh_node<G>(m, at, i, j, sub, p);
-        if (n < kNodes && sub == 0) {
-            kind[n] = k;
-            if (node) {
+        kind[n] = mesh_node<1, false>(m, i, j, 0, p);
 #pragma unroll
-                for (int r = 0; r < 3; ++r) v[n][r] = p[r];
-                if ((a < kQuadBlock || i == m.gh - 1) && (b < kQuadBlock || j == m.gw - 1)) {
-                    float* o = xyz + 3 * ((int64_t)i * m.gw + j);
+        for (int r = 0; r < 3; ++r) v[n][r] = p[r];
+        if ((na < kQuadBlock || i == m.gh - 1) && (nb < kQuadBlock || j == m.gw - 1)) {
+            float* o = xyz + 3 * ((int64_t)i * m.gw + j);
 #pragma unroll
-                    for (int r = 0; r < 3; ++r) o[r] = p[r];
-                }
-            }
+            for (int r = 0; r < 3; ++r) o[r] = p[r];
         }
     }
     __syncthreads();
@@ -146,35 +137,70 @@ __global__ void __launch_bounds__(kWG) k_mesh_block(MeshArgs m, int bw, double l
     bool keep = i0 + a < m.gh - 1 && j0 + b < m.gw - 1, fu = false;
     const int n00 = a * kNodeSide + b;
     const int c[4] = {n00, n00 + 1, n00 + kNodeSide + 1, n00 + kNodeSide};   // perimeter order
-    if (keep) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int kk = kind[c[k]];
-            keep &= kk != kDead;
-            fu |= kk == kNoReturn;
-            const float* p = v[c[k]];
-            const float* q = v[c[(k + 1) & 3]];
-            const double dx = (double)p[0] - (double)q[0];
-            const double dy = (double)p[1] - (double)q[1];
-            const double dz = (double)p[2] - (double)q[2];
-            fu |= ((dx * dx + dy * dy) + dz * dz) > lim2;
-        }
-    }
+    if (keep) quad_test(c, [&](int n) { return kind[n]; }, [&](int n) { return v[n]; }, lim2, keep, fu);
     const uint64_t mk = __ballot(keep), mf = __ballot(keep && fu);
     if (lane == 0) { masks[2 * (int64_t)blk] = mk; masks[2 * (int64_t)blk + 1] = mf; }
 }
 
-// Exclusive prefix sum of the block counts (one workgroup of 1024 threads),
-// for grids of more than kDirectBlocks blocks.
+// Nodes by themselves, G lanes each: all that have windows, large grids, and
+// grids without quads (a single row or column of nodes; kind null, the triangle
+// total is zero).
+template <int G, bool WIN>
+__global__ void __launch_bounds__(kWG) k_mesh_nodes(MeshArgs m, float* __restrict__ xyz, uint8_t* __restrict__ kind,
+                                                    int32_t* __restrict__ total) {
+    const int64_t t = (int64_t)blockIdx.x * kWG + threadIdx.x, n = t / G;
+    if (!kind && t == 0) *total = 0;
+    if (n >= (int64_t)m.gh * m.gw) return;
+    float p[3];
+    const int k = mesh_node<G, WIN>(m, (int)(n / m.gw), (int)(n % m.gw), (int)(t % G), p);
+    if (t % G) return;
+    if (kind) kind[n] = (uint8_t)k;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) xyz[3 * n + r] = p[r];
+}
+
+// A window's rows go to as many lanes as leave the launch within about half a
+// million threads: 9x9 windows of 300 / 1,200 / 2,451 / 4,800 blocks take 35.9 /
+// 43.9 / 49.7 / 73.5 us a view with eight lanes, 36.2 / 39.5 / 45.2 / 60.2 with
+// two and 38.6 / 41.9 / 46.2 / 58.5 with one; 33x33 windows of 300 / 2,451 /
+// 4,800 blocks 58 / 127 / 326, 66 / 118 / 212 and 94 / 130 / 181 us.  Whole
+// blocks in one workgroup with their windows staged in LDS took 38 / 45 / 54 /
+// 77 and 64 / 134 / 222 us: corners on shared sides computed twice to four
+// times, and at large strides more pixels staged than used.
+constexpr int64_t kEightLanes = 512, kTwoLanes = 4096;
+
+// The masks of k_mesh_block from nodes in memory, a wave per block of quads;
+// counts (may be null): its triangles.
+__global__ void __launch_bounds__(kWG) k_mesh_quads(const float* __restrict__ xyz, const uint8_t* __restrict__ kind,
+                                                    int gh, int gw, int bw, int64_t n_blocks, double lim2,
+                                                    uint64_t* __restrict__ masks, int32_t* __restrict__ counts) {
+    const int64_t blk = (int64_t)blockIdx.x * (kWG / 64) + threadIdx.x / 64;
+    const int lane = threadIdx.x & 63;
+    if (blk >= n_blocks) return;
+    const int qi = (int)(blk / bw) * kQuadBlock + lane / kQuadBlock, qj = (int)(blk % bw) * kQuadBlock + lane % kQuadBlock;
+    bool keep = qi < gh - 1 && qj < gw - 1, fu = false;
+    const int64_t n00 = (int64_t)qi * gw + qj;
+    const int64_t c[4] = {n00, n00 + 1, n00 + gw + 1, n00 + gw};
+    if (keep) quad_test(c, [&](int64_t n) { return (int)kind[n]; }, [&](int64_t n) { return xyz + 3 * n; }, lim2, keep, fu);
+    const uint64_t mk = __ballot(keep), mf = __ballot(keep && fu);
+    if (lane == 0) {
+        masks[2 * blk] = mk;
+        masks[2 * blk + 1] = mf;
+        if (counts) counts[blk] = 2 * __popcll(mk);
+    }
+}
+
+// Exclusive prefix sum of the block counts in place (one workgroup of 1024
+// threads), for grids of more than kDirectBlocks blocks.
 constexpr int64_t kDirectBlocks = 4096;
 
-__global__ void k_mesh_scan(const uint64_t* __restrict__ masks, int64_t n, int32_t* __restrict__ offsets) {
+__global__ void k_mesh_scan(int32_t* __restrict__ offsets, int64_t n) {
     __shared__ int64_t part[1024];
     const int t = threadIdx.x;
     const int64_t per = (n + 1023) / 1024;
     const int64_t b = t * per, e = b + per < n ? b + per : n;
     int64_t s = 0;
-    for (int64_t k = b; k < e; ++k) s += 2 * __popcll(masks[2 * k]);
+    for (int64_t k = b; k < e; ++k) s += offsets[k];
     part[t] = s;
     __syncthreads();
     for (int off = 1; off < 1024; off <<= 1) {
@@ -184,7 +210,11 @@ __global__ void k_mesh_scan(const uint64_t* __restrict__ masks, int64_t n, int32
         __syncthreads();
     }
     int64_t run = part[t] - s;
-    for (int64_t k = b; k < e; ++k) { offsets[k] = (int32_t)run; run += 2 * __popcll(masks[2 * k]); }
+    for (int64_t k = b; k < e; ++k) {
+        const int32_t c = offsets[k];
+        offsets[k] = (int32_t)run;
+        run += c;
+    }
 }
 
 // Triangles of four blocks per workgroup, a wave each.  Without offsets
@@ -224,17 +254,6 @@ __global__ void __launch_bounds__(kWG) k_mesh_emit(const uint64_t* __restrict__ 
     tri[3 * t0 + 3] = n00; tri[3 * t0 + 4] = n11; tri[3 * t0 + 5] = n10;
     cls[t0] = c;
     cls[t0 + 1] = c;
-}
-
-// A grid without quads (a single row or column of nodes).
-__global__ void k_mesh_nodes(MeshArgs m, float* __restrict__ xyz, int32_t* __restrict__ total) {
-    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n == 0) *total = 0;
-    if (n / 8 >= (int64_t)m.gh * m.gw) return;
-    float p[3];
-    mesh_node<8>(m, [&](int y, int x) { return m.depth[(int64_t)y * m.W + x]; }, (int)(n / 8 / m.gw), (int)(n / 8 % m.gw), (int)(n % 8), p);
-    if (n % 8 == 0)
-        for (int r = 0; r < 3; ++r) xyz[3 * (n / 8) + r] = p[r];
 }
 
 // Cluster bounds: one workgroup per cluster of kClusterTris triangles.
@@ -316,7 +335,7 @@ hipError_t launch_scan_image(hipStream_t st, const float* depth, int32_t H, int3
 hipError_t launch_meshify(hipStream_t st, const float* depth, rm_camera cam, const double* T,
                           int32_t stride, int32_t smooth_radius, float z_min, float z_max, float max_edge,
                           float* xyz, int32_t* tri, uint8_t* cls, int64_t cap_t, uint64_t* masks,
-                          int32_t* block_offsets, int32_t* total) {
+                          uint8_t* kind, int32_t* block_offsets, int32_t* total) {
     MeshArgs m;
     m.depth = depth;
     m.H = cam.height; m.W = cam.width; m.s = stride; m.R = smooth_radius;
@@ -328,22 +347,25 @@ hipError_t launch_meshify(hipStream_t st, const float* depth, rm_camera cam, con
     const int64_t nb = meshify_blocks(m.H, m.W, stride);
     const int bw = (m.gw - 1 + kQuadBlock - 1) / kQuadBlock;
     const double lim2 = (double)max_edge * (double)max_edge;
+    auto blocks = [&](int lanes) { return dim3((unsigned)((lanes * nn + kWG - 1) / kWG)); };
     if (nb == 0) {
-        hipLaunchKernelGGL(k_mesh_nodes, dim3((unsigned)((8 * nn + 255) / 256)), dim3(256), 0, st, m, xyz, total);
+        hipLaunchKernelGGL((k_mesh_nodes<8, true>), blocks(8), dim3(kWG), 0, st, m, xyz, (uint8_t*)nullptr, total);
         return hipGetLastError();
     }
-    const int patch = kQuadBlock * stride + 2 * smooth_radius + 1;
-    const dim3 grid((unsigned)nb);
-    if (smooth_radius == 0)
-        hipLaunchKernelGGL((k_mesh_block<1, false>), grid, dim3(kWG), 0, st, m, bw, lim2, 0, xyz, masks);
-    else if (patch <= kMaxPatch)
-        hipLaunchKernelGGL((k_mesh_block<8, true>), grid, dim3(kWG), (size_t)patch * patch * sizeof(float), st, m, bw,
-                           lim2, patch, xyz, masks);
-    else
-        hipLaunchKernelGGL((k_mesh_block<8, false>), grid, dim3(kWG), 0, st, m, bw, lim2, 0, xyz, masks);
     const bool direct = nb <= kDirectBlocks;
-    if (!direct) hipLaunchKernelGGL(k_mesh_scan, dim3(1), dim3(1024), 0, st, masks, nb, block_offsets);
-    hipLaunchKernelGGL(k_mesh_emit, dim3((unsigned)((nb + 3) / 4)), dim3(kWG), 0, st, masks, m.gw, bw, nb,
+    const dim3 waves((unsigned)((nb + 3) / 4));
+    if (smooth_radius == 0 && direct) {
+        hipLaunchKernelGGL(k_mesh_block, dim3((unsigned)nb), dim3(kWG), 0, st, m, bw, lim2, xyz, masks);
+    } else {
+        if (smooth_radius == 0) hipLaunchKernelGGL((k_mesh_nodes<1, false>), blocks(1), dim3(kWG), 0, st, m, xyz, kind, total);
+        else if (nb <= kEightLanes) hipLaunchKernelGGL((k_mesh_nodes<8, true>), blocks(8), dim3(kWG), 0, st, m, xyz, kind, total);
+        else if (nb <= kTwoLanes) hipLaunchKernelGGL((k_mesh_nodes<2, true>), blocks(2), dim3(kWG), 0, st, m, xyz, kind, total);
+        else hipLaunchKernelGGL((k_mesh_nodes<1, true>), blocks(1), dim3(kWG), 0, st, m, xyz, kind, total);
+        hipLaunchKernelGGL(k_mesh_quads, waves, dim3(kWG), 0, st, xyz, kind, m.gh, m.gw, bw, nb, lim2, masks,
+                           direct ? nullptr : block_offsets);
+    }
+    if (!direct) hipLaunchKernelGGL(k_mesh_scan, dim3(1), dim3(1024), 0, st, block_offsets, nb);
+    hipLaunchKernelGGL(k_mesh_emit, waves, dim3(kWG), 0, st, masks, m.gw, bw, nb,
                        direct ? nullptr : block_offsets, cap_t, tri, cls, total);
     return hipGetLastError();
 }

@@ -1,8 +1,8 @@
-"""Every form of the meshing and normals kernels: windows staged in LDS up to
-the largest that is (88 px a side: stride 8 with radius 11 is 87, radius 12 is
-89), windows read from memory, strides above one on ragged images, grids of as
-many blocks as the triangle pass sums in place (4,096) and more, normals of every
-radius; and the union of meshes of which some are empty."""
+"""Every form of the meshing and normals kernels: windows of every kind of size
+at strides above one on ragged images, their rows shared by eight lanes (up to
+512 blocks of quads), two (up to 4,096) or one, grids without windows of as many
+blocks as one workgroup takes whole (4,096) and more, normals of every radius;
+and the union of meshes of which some are empty."""
 import numpy as np
 import pytest
 
@@ -48,9 +48,11 @@ def test_meshing_windows_bitexact(rm, H, W, stride, radius):
     assert _mesh_bitexact(rm, H, W, stride, radius) > 0
 
 
-@pytest.mark.parametrize("H,W", [(513, 513), (513, 514)])
-def test_meshing_block_offsets_bitexact(rm, H, W):
-    assert _mesh_bitexact(rm, H, W, 1, 0) > 100_000
+@pytest.mark.parametrize("radius", [0, 1, 2])
+@pytest.mark.parametrize("H,W", [(129, 257), (137, 257), (513, 513), (513, 514)])
+def test_meshing_block_offsets_bitexact(rm, H, W, radius):
+    """16 x 32 = 512 blocks and 17 x 32, 64 x 64 = 4,096 and 64 x 65."""
+    assert _mesh_bitexact(rm, H, W, 1, radius) > 30_000
 
 
 @pytest.mark.parametrize("radius", range(9))
