@@ -436,7 +436,8 @@ int rm_depth_downsample(rm_ctx* ctx, const float* depth, int32_t height, int32_t
  *   depth    device [H][W] f32, NaN = invalid
  *   normals  device [H][W][3] f32; NaN on the image border and where the
  *            pixel or one of its four difference neighbours is invalid.
- * sigma > 0; radius in 0..RM_MAX_NORMAL_RADIUS. */
+ * sigma > 0; radius in 0..RM_MAX_NORMAL_RADIUS.  Long, narrow images may use
+ * 8 H W bytes of the context's scratch, where it is there or can grow. */
 #define RM_MAX_NORMAL_RADIUS 8
 int rm_depth_normals(rm_ctx* ctx, const float* depth, int32_t height, int32_t width, float fx, float fy,
                      float sigma, int32_t radius, float* normals);

@@ -1056,7 +1056,16 @@ int rm_depth_normals(rm_ctx* ctx, const float* depth, int32_t height, int32_t wi
     }
     for (int k = 0; k <= 2 * radius; ++k) gw.w[k] /= sum;
     DeviceGuard g(ctx->device);
-    RM_HIP(ctx, launch_depth_normals(ctx->stream, depth, height, width, (double)fx, (double)fy, gw, normals));
+    // (the other form needs no scratch: under capture or out of memory it takes over)
+    double* smoothed = nullptr;
+    const size_t bytes = (size_t)height * width * sizeof(double);
+    if (normals_in_two(height, width, radius) && (bytes <= ctx->scratch_size || !capturing(ctx))) {
+        const int rc = ensure_scratch(ctx, bytes);
+        if (rc && rc != RM_ERR_OOM) return rc;
+        if (rc) ctx->err.clear();
+        else smoothed = at<double>(ctx, 0);
+    }
+    RM_HIP(ctx, launch_depth_normals(ctx->stream, depth, height, width, (double)fx, (double)fy, gw, smoothed, normals));
     return RM_OK;
 }
 

@@ -20,19 +20,39 @@ __global__ void k_downsample(const float* __restrict__ depth, int32_t H, int32_t
     out[n] = (z > 0.0f && z <= z_max) ? z : __int_as_float(0x7fc00000);   // NaN and +inf fail both tests
 }
 
-// Gaussian smoothing over the valid pixels of the (2R+1)^2 window, weights
-// w_a w_b renormalized over them (FP64); an invalid centre stays NaN.  Then
 // Eq. (2): with the central differences dz_x, dz_y of the smoothed depth and
 // the metric steps dx = 2 z/fx, dy = 2 z/fy at the centre, the normal is
 // (0, dy, dz_y) x (dx, 0, dz_x) = (dy dz_x, dx dz_y, -dx dy), normalized
-// (camera frame).  NaN on the border and where an input is invalid.
+// (camera frame).  s: the smoothed depth at the pixel, rows `row` apart; NaN
+// inputs give NaN.
+__device__ __forceinline__ float3 depth_normal(const double* s, int row, double fx, double fy) {
+    const double c = *s;
+    const double dzx = s[1] - s[-1];
+    const double dzy = s[row] - s[-row];
+    const double dx = 2.0 * c / fx, dy = 2.0 * c / fy;
+    const double a = dy * dzx, b = dx * dzy, e = -dx * dy;
+    const double inv = 1.0 / sqrt(a * a + b * b + e * e);
+    return make_float3((float)(a * inv), (float)(b * inv), (float)(e * inv));
+}
+
+// Gaussian smoothing over the valid pixels of the (2R+1)^2 window, weights
+// w_a w_b renormalized over them (FP64); an invalid centre stays NaN.  Then
+// Eq. (2); NaN on the border and where an input is invalid.
 // One workgroup per 32x8 pixels: depths with a border of R + 1 and smoothed
 // depths with a border of one stay in LDS (340 smoothed pixels for 256
 // normals); the radius is known when compiled, so that a window's loads and
 // sums are straight code (latency bounds the pass).  320x240, R = 2: 6.0 us;
-// 13.8 us in two launches with the smoothed image in memory.
+// 13.8 us in two launches with the smoothed image in memory.  Windows up to
+// R = 5 are written out whole, of larger ones five rows at a time: the products
+// of all their weights, kept in registers, leave too few waves (640x480, R = 8:
+// 51 us a call, 110 us with 362 registers, 63 us in two launches; 1280x960, R =
+// 6: 97, 113 and 129 us, though 320x240 took 17.2 us whole and takes 19.2).
 constexpr int kNrmW = 32, kNrmH = 8;
 constexpr int kNrmPW = kNrmW + 2 * (RM_MAX_NORMAL_RADIUS + 1), kNrmPH = kNrmH + 2 * (RM_MAX_NORMAL_RADIUS + 1);
+
+constexpr int kUnrolled = 5, kPartUnroll = 5;
+template <int R>
+constexpr int kRowUnroll = R <= kUnrolled ? 2 * R + 1 : kPartUnroll;
 
 template <int R>
 __global__ void __launch_bounds__(kWG) k_depth_normals(const float* __restrict__ depth, int32_t H, int32_t W, GaussW g,
@@ -56,7 +76,7 @@ __global__ void __launch_bounds__(kWG) k_depth_normals(const float* __restrict__
         double s = (double)q;
         if (*c == *c) {
             double num = 0.0, den = 0.0;
-#pragma unroll
+#pragma unroll kRowUnroll<R>
             for (int a = -R; a <= R; ++a) {
                 const double wa = g.w[a + R];
 #pragma unroll
@@ -75,19 +95,51 @@ __global__ void __launch_bounds__(kWG) k_depth_normals(const float* __restrict__
     __syncthreads();
     const int lx = threadIdx.x % kNrmW, ly = threadIdx.x / kNrmW, x = bx + lx, y = by + ly;
     if (x >= W || y >= H) return;
-    float o0 = q, o1 = q, o2 = q;
-    if (x > 0 && x < W - 1 && y > 0 && y < H - 1) {
-        const double* s = zs + (ly + 1) * (kNrmW + 2) + lx + 1;
-        const double c = *s;
-        const double dzx = s[1] - s[-1];
-        const double dzy = s[kNrmW + 2] - s[-(kNrmW + 2)];
-        const double dx = 2.0 * c / fx, dy = 2.0 * c / fy;
-        const double a = dy * dzx, b = dx * dzy, e = -dx * dy;
-        const double inv = 1.0 / sqrt(a * a + b * b + e * e);   // NaN inputs give NaN
-        o0 = (float)(a * inv); o1 = (float)(b * inv); o2 = (float)(e * inv);
+    float3 o = make_float3(q, q, q);
+    if (x > 0 && x < W - 1 && y > 0 && y < H - 1)
+        o = depth_normal(zs + (ly + 1) * (kNrmW + 2) + lx + 1, kNrmW + 2, fx, fy);
+    float* n = nrm + 3 * ((int64_t)y * W + x);
+    n[0] = o.x; n[1] = o.y; n[2] = o.z;
+}
+
+// The same in two launches, the smoothed image in memory, for long images that
+// fill little of a 32x8 tile (normals_in_two).
+__global__ void __launch_bounds__(kWG) k_smooth(const float* __restrict__ depth, int32_t H, int32_t W, GaussW g,
+                                                double* __restrict__ out) {
+    const int64_t n = (int64_t)blockIdx.x * kWG + threadIdx.x;
+    if (n >= (int64_t)H * W) return;
+    const int y = (int)(n / W), x = (int)(n % W);
+    double s = (double)__int_as_float(0x7fc00000);
+    if (depth[n] == depth[n]) {
+        double num = 0.0, den = 0.0;
+        for (int a = -g.radius; a <= g.radius; ++a) {
+            const int yy = y + a;
+            if (yy < 0 || yy >= H) continue;
+            const double wa = g.w[a + g.radius];
+            for (int b = -g.radius; b <= g.radius; ++b) {
+                const int xx = x + b;
+                if (xx < 0 || xx >= W) continue;
+                const float z = depth[(int64_t)yy * W + xx];
+                if (!(z == z)) continue;
+                const double w = wa * g.w[b + g.radius];
+                num += w * (double)z;
+                den += w;
+            }
+        }
+        s = num / den;
     }
-    float* o = nrm + 3 * ((int64_t)y * W + x);
-    o[0] = o0; o[1] = o1; o[2] = o2;
+    out[n] = s;
+}
+
+__global__ void __launch_bounds__(kWG) k_normals(const double* __restrict__ zs, int32_t H, int32_t W, double fx, double fy,
+                                                 float* __restrict__ nrm) {
+    const int64_t n = (int64_t)blockIdx.x * kWG + threadIdx.x;
+    if (n >= (int64_t)H * W) return;
+    const int y = (int)(n / W), x = (int)(n % W);
+    const float q = __int_as_float(0x7fc00000);
+    float3 o = make_float3(q, q, q);
+    if (x > 0 && x < W - 1 && y > 0 && y < H - 1) o = depth_normal(zs + n, W, fx, fy);
+    nrm[3 * n] = o.x; nrm[3 * n + 1] = o.y; nrm[3 * n + 2] = o.z;
 }
 
 struct Rot9 { double r[9]; };
@@ -117,8 +169,23 @@ hipError_t launch_downsample(hipStream_t st, const float* depth, int32_t H, int3
     return hipGetLastError();
 }
 
+// Images of at least 2^16 pixels that are less than 8 pixels wide, or with R > 2
+// less than 24 wide or 8 high: 3 x 200,000 pixels take 14 us in two launches
+// and 32 in one at R = 0, 59 and 677 at R = 8; 15 x 20,000 13.5 and 12.9 at R = 2,
+// 23 and 29 at R = 4; 31 x 9,000 60 and 51 at R = 8; 200,000 x 3 15.0 and 15.4 at
+// R = 2, 28 and 106 at R = 8.
+bool normals_in_two(int32_t H, int32_t W, int32_t radius) {
+    return (int64_t)H * W >= 65536 && (W < 8 || (radius > 2 && (W < 24 || H < 8)));
+}
+
 hipError_t launch_depth_normals(hipStream_t st, const float* depth, int32_t H, int32_t W, double fx, double fy,
-                                const GaussW& g, float* normals) {
+                                const GaussW& g, double* smoothed, float* normals) {
+    if (smoothed) {
+        const unsigned nb = blocks_for((int64_t)H * W);
+        hipLaunchKernelGGL(k_smooth, dim3(nb), dim3(kWG), 0, st, depth, H, W, g, smoothed);
+        hipLaunchKernelGGL(k_normals, dim3(nb), dim3(kWG), 0, st, smoothed, H, W, fx, fy, normals);
+        return hipGetLastError();
+    }
     const dim3 grid((unsigned)((W + kNrmW - 1) / kNrmW) * (unsigned)((H + kNrmH - 1) / kNrmH));
 #define RM_NRM(R)                                                                                                  \
     case R: hipLaunchKernelGGL(k_depth_normals<R>, grid, dim3(kWG), 0, st, depth, H, W, g, fx, fy, normals); break;

@@ -172,8 +172,11 @@ struct GaussW {
 };
 hipError_t launch_downsample(hipStream_t st, const float* depth, int32_t H, int32_t W, int32_t f, float z_max,
                              float* out);
+// smoothed: [H][W] f64 scratch for the two-launch form, null for the other;
+// normals_in_two says which is faster.
+bool normals_in_two(int32_t H, int32_t W, int32_t radius);
 hipError_t launch_depth_normals(hipStream_t st, const float* depth, int32_t H, int32_t W, double fx, double fy,
-                                const GaussW& g, float* normals);
+                                const GaussW& g, double* smoothed, float* normals);
 // T_wc: host, 12 doubles
 hipError_t launch_vertex_normals(hipStream_t st, const float* normals, int32_t H, int32_t W, int32_t stride,
                                  const double* T_wc, float* out);
