@@ -1903,31 +1903,39 @@ hipError_t launch_bin_shape(hipStream_t st, const BatchDesc& bd, const RasterArg
 
 constexpr int kOrderBuckets = 32;
 
-// Share of a workgroup: the call's entries over its resident workgroups, at
-// least kMinSlice.  Where the fullest record holds kCutAbove shares, records
-// above the share are cut into slices of about that many entries, so that few
-// or uneven tiles still fill the device: one pose of 640x480 is 150 records
-// whose fullest one used to set the time (350 us of rasterizing; 164 and 24 us
-// of merging in slices).  A slice starts with an empty z-buffer and culls less
-// than the whole record would (1.4 times the instructions there), so cutting
-// does not pay where whole records fill most of the device.  Calls against 1 M
-// triangles, cut and whole: 249 and 433 us with 26 shares in the fullest record
-// (one pose), 421 and 523 us with 6.4 (four), 580 and 566 us with 4.1 (six),
-// 651 and 610 us with 3.1 (eight); 16 ICP pairs with 2.9 shares 164 and 133 us;
-// light calls pay the merge longer (one to four poses of 150,000 entries each,
-// 9 to 10 shares, 1 to 6 % more).  Slices of half the share made 32 ICP pairs
+// Share of a workgroup: the call's entries over its resident workgroups.  Where
+// the fullest record would set the time, records above the share (and
+// kMinSlice) are cut into slices of about that many entries, so that few or
+// uneven tiles still fill the device: one pose of 640x480 is 150 records whose
+// fullest one used to take 350 us of rasterizing; 161 us in slices and 22 of
+// merging.  A slice starts with an empty z-buffer and culls less than the whole
+// record would (1.4 times the instructions there), and a workgroup left alone
+// on its CU is up to four times as fast as one of four, so cutting pays from
+// kCutHalves / 2 shares in the fullest record on.  To a share counts what a
+// record costs beside its entries, as much as kRecordCost of them at 64x32
+// pixels (empty records cost next to nothing); kMergeCost more pay for the merge
+// launch.  Cut and whole, fullest record and line: 64 poses of 160x120 against
+// 340 k triangles 663 and 784 us (37,000; 28,700), 16 poses of 320x240 338 and 438
+// (16,600; 11,500), 4 poses of 640x480 against 1 M 414 and 521 (18,300; 10,500), 6
+// poses 585 and 569 (18,300; 15,600), 8 poses 636 and 607 (18,300; 20,300), 6 poses
+// against 186 k 282 and 239 (4,300; 6,800), 8 ICP pairs 126 and 111 (3,960; 4,020).
+// Over 81 such calls the line costs 0.4 % of the better form on average, cutting
+// every record above a share 2.4 %.  Slices of half the share made 32 ICP pairs
 // slower (329 against 287 us a call) and one pose no faster.
 constexpr int kMinSlice = 2 * kWG;
-constexpr int kCutAbove = 6;
+constexpr int kCutHalves = 5, kRecordCost = 1600, kMergeCost = 1024;
 
 // hist: [0, 32) bucket counts, [32, 64) cursors; while the order is made,
-// a.queue[0]: entries of the call in units of 64, a.queue[2]: the fullest record
-__device__ __forceinline__ uint32_t slice_size(uint32_t total64, uint32_t fullest, int resident) {
-    const uint32_t size = (uint32_t)max((int64_t)kMinSlice, (int64_t)total64 * 64 / resident);
-    return fullest >= (uint64_t)kCutAbove * size ? size : 0xffffffffu;
+// a.queue[0]: entries of the call in units of 64, a.queue[2]: the fullest
+// record.  busy: records with entries; tile_px: pixels of a tile.
+__device__ __forceinline__ uint32_t slice_size(uint32_t total64, uint32_t fullest, int64_t busy, int tile_px, int resident) {
+    const int64_t total = (int64_t)total64 * 64;
+    const int64_t cost = total + busy * (kRecordCost * tile_px / 2048);
+    if (2 * (int64_t)resident * ((int64_t)fullest - kMergeCost) < kCutHalves * cost) return 0xffffffffu;
+    return (uint32_t)max((int64_t)kMinSlice, total / resident);
 }
 
-// bucket 0 holds the costliest records: 31 - floor(log2(fill + 1))
+// bucket 0 holds the costliest records: 31 - floor(log2(fill + 1)); the last one the empty ones
 __device__ __forceinline__ int order_bucket(uint32_t fill) { return __clz((int)(fill + 1u)); }
 
 // Record at position `item` of the item order (per scan tile-major, poses of a
@@ -2017,7 +2025,8 @@ __global__ void __launch_bounds__(kOrderWG) k_order_one(BatchDesc bd, const int3
         if (tid < kOrderBuckets) cur[tid] = inc - c;
     }
     __syncthreads();
-    const uint32_t size = slice_size(total, (uint32_t)fullest, resident);
+    const uint32_t size = slice_size(total, (uint32_t)fullest, n - cnt[kOrderBuckets - 1],
+                                     bd.tile_w * bd.tile_h, resident);
     for (int i0 = 0; i0 < n; i0 += kOrderWG) {
         const int item = i0 + tid;
         const bool live = item < n;
@@ -2058,14 +2067,15 @@ __global__ void __launch_bounds__(kWG) k_order_count(const int32_t* __restrict__
 
 // hist[0..31] counts -> hist[32..63] running cursors (exclusive prefix); the
 // slice size in their place, and the queue starts from zero
-__global__ void k_order_offsets(int32_t* hist, int32_t* queue, int resident) {
+__global__ void k_order_offsets(int32_t* hist, int32_t* queue, int64_t n, int tile_px, int resident) {
     if (threadIdx.x != 0) return;
     int acc = 0;
     for (int k = 0; k < kOrderBuckets; ++k) {
         hist[kOrderBuckets + k] = acc;
         acc += hist[k];
     }
-    hist[0] = (int32_t)slice_size((uint32_t)queue[0], (uint32_t)queue[2], resident);
+    hist[0] = (int32_t)slice_size((uint32_t)queue[0], (uint32_t)queue[2], n - hist[kOrderBuckets - 1], tile_px,
+                                  resident);
     queue[0] = 0;
 }
 
@@ -2171,7 +2181,8 @@ hipError_t launch_order(hipStream_t st, const BatchDesc& bd, const RasterArgs& a
     const unsigned g = (unsigned)((n_records + kWG - 1) / kWG);
     hipLaunchKernelGGL(k_order_count, dim3(g), dim3(kWG), 0, st, a.bin_small, a.bin_big, n_records, hist, a.queue,
                        a.bin_max);
-    hipLaunchKernelGGL(k_order_offsets, dim3(1), dim3(64), 0, st, hist, a.queue, resident);
+    hipLaunchKernelGGL(k_order_offsets, dim3(1), dim3(64), 0, st, hist, a.queue, n_records,
+                       bd.tile_w * bd.tile_h, resident);
     hipLaunchKernelGGL(k_order_scatter, dim3(g), dim3(kWG), 0, st, bd, a.bin_small, a.bin_big, n_records, hist, split,
                        a.split_cap, a.queue, order);
     return hipGetLastError();

@@ -8,7 +8,7 @@ import re
 import numpy as np
 import pytest
 
-from gpu_helpers import EPS, oracle_map, workload
+from gpu_helpers import EPS, workload
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -18,8 +18,9 @@ def _setup(n_away):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_1702_06813_amd as rm
-    w = workload("kinect")
-    mesh = rm.Mesh.from_arrays(*oracle_map("kinect")).prepare()
+    w = workload("differentiation")
+    mesh = rm.Mesh.concat([rm.mesh_from_range(torch.from_numpy(z).cuda(), w.cam, V, w.stride, w.z_min, w.z_max, w.max_edge,
+                                              w.smooth_radius) for V, z in zip(w.views, w.view_depths)]).prepare()
     scan = rm.scan_image(torch.from_numpy(w.scan_depth).cuda(), cam=w.cam)
     away = np.array(w.poses[0], np.float64).reshape(3, 4).copy()
     away[:, 3] += 1000.0
