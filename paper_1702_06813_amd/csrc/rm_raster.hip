@@ -130,14 +130,17 @@ __device__ __forceinline__ PlaneN plane_normal(const PoseF& P, const float v[9])
     return q;
 }
 
-// 1/z over the image: w(u, v) = a (u - cx) + b (v - cy) + e.
-// False for a plane through the camera centre (c = 0), which has no depth.
-__device__ __forceinline__ bool depth_plane(const PlaneN& q, double ifx, double ify, WPlane& p) {
+// 1/z over the image: w(u, v) = a (u - cx) + b (v - cy) + e, of a plane whose |c| is
+// above kMinC (1/c is finite there).
+constexpr double kMinC = 1e-300;
+
+__device__ __forceinline__ WPlane depth_plane(const PlaneN& q, double ifx, double ify) {
     const double ic = 1.0 / q.c;
+    WPlane p;
     p.a = q.nx * ic * ifx;
     p.b = q.ny * ic * ify;
     p.e = q.nz * ic;
-    return fabs(ic) < (double)INFINITY;
+    return p;
 }
 
 struct Tile {
@@ -552,24 +555,29 @@ __device__ __forceinline__ int setup_triangle(uint64_t* keys, WaveQueue& q, int 
     // the round start, no pixel of the triangle can change:
     // (1/z_min + |a| + |b|) (1 + 1e-5) < w_key.  Outside ICP mode the test is
     // taken multiplied by z_min |c| > 0, so that a skipped triangle needs no
-    // division (a plane through the camera centre, c = 0, is left out after it);
+    // division;
     // in ICP mode the plane first (fewer registers live across the test there).
+    // A plane through the camera centre (c = 0) has no depth and is left out in the
+    // same branches.
     const float wt = fminf(fminf(rmin[kSnapTile], rmin[kSnapTile + 1]), fminf(rmin[kSnapTile + 2], rmin[kSnapTile + 3]));
+    const double ac = fabs(pn.c);
     WPlane pl;
     if constexpr (MODE == kIcp) {
-        if (!depth_plane(pn, ifx, ify, pl)) return 0;
+        if (!(ac > kMinC)) return 0;
+        pl = depth_plane(pn, ifx, ify);
         if (nin == 3) {
             const double wv = 1.0 / (double)fminf(V0.z, fminf(V1.z, V2.z)) + fabs(pl.a) + fabs(pl.b);
             if (wv * 1.00001 < (double)wt) return 0;
         }
     } else {
+        bool out = !(ac > kMinC);
         if (nin == 3) {
             const double zmin = (double)fminf(V0.z, fminf(V1.z, V2.z));
-            const double ac = fabs(pn.c);
             const double lhs = (ac + zmin * (fabs(pn.nx * ifx) + fabs(pn.ny * ify))) * 1.00001;
-            if (lhs < (double)wt * zmin * ac) return 0;
+            out |= lhs < (double)wt * zmin * ac;
         }
-        if (!depth_plane(pn, ifx, ify, pl)) return 0;
+        if (out) return 0;
+        pl = depth_plane(pn, ifx, ify);
     }
     const uint32_t id = (uint32_t)in.t;
     // near-plane clip into at most two sub-triangles; one emit call site keeps
