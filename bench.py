@@ -34,17 +34,17 @@ HBM_PEAK_GBS = 8000.0
 # scaled by a plain-copy calibration (profiles/k_raster_differentiation.md);
 # valid only for the rasterizer source and tile they were taken with (the
 # prefix moves with a comment-only edit whose device assembly is unchanged).
-PROFILED_TRAFFIC = {"rm_raster_sha256_16": "06b5f7743d9564cf", "tile": [64, 32],
+PROFILED_TRAFFIC = {"rm_raster_sha256_16": "831135080a4d16f2", "tile": [64, 32],
                     # calibrated FETCH_SIZE + WRITE_SIZE of one rasterizer and one
                     # binning launch, and the rasterizer's VALU issue fraction
                     # (profiles/k_raster_differentiation.md)
-                    "bytes_per_launch": 1474.5e6, "bin_bytes_per_launch": 1218.8e6, "valu_issue_frac": 0.861,
+                    "bytes_per_launch": 1494.1e6, "bin_bytes_per_launch": 1218.7e6, "valu_issue_frac": 0.861,
                     # SQ_INSTS_LDS_ATOMIC_BANDWIDTH x 8: 64-bit LDS atomic lanes of one
                     # rasterizer launch (an upper bound: the few other LDS atomics
                     # count as well), and TCC_ATOMIC_sum of one binning launch and its
                     # profiled duration (profiles/atomics_differentiation.md)
-                    "lds_atomic_lanes_per_launch": 1.366e8, "bin_global_atomics_per_launch": 7.444e5,
-                    "bin_launch_ms": 0.957}
+                    "lds_atomic_lanes_per_launch": 1.372e8, "bin_global_atomics_per_launch": 7.444e5,
+                    "bin_launch_ms": 0.959}
 
 
 def profiled_traffic(tile, field="bytes_per_launch"):
